@@ -972,8 +972,8 @@ constexpr int kBWaves = 8;
 constexpr int kBThreads = kBWaves * kWave;
 constexpr int kBRing = 7;                          // tile slots: the two being read, up to five in flight
 constexpr int kBMaxPieces = 64;                    // branches per unit (host-checked)
-// a workgroup's range holds at most kMaxSplitKeys entries, each piece pads its last tile, and the
-// prefetches run kBRing tiles past the end
+// a workgroup's entries, the padding of each piece's last tile (kMaxSplitKeys entries fit beside the
+// padding of kBMaxPieces pieces, more beside fewer) and the kBRing tiles the prefetches run past the end
 constexpr int kBSlotCap = kMaxSplitKeys + (kBMaxPieces + kBRing) * kTile;
 // a block-mode tile: K in the score operand order (8 KiB), then V row-major for the transposing reads
 constexpr int kBTileBytes = 8192 + kRmTileBytes;
@@ -1259,6 +1259,8 @@ __device__ inline int block_branch_len(const AttnParams& p, int s, int L, int b)
 // Block mode's cut of a unit's key stream (StreamCut): measured, a tile of gathered rows takes
 // 1.78 us of a workgroup's loop and a contiguous one 1.43 us.
 constexpr int kWGather = 5, kWFull = 4;
+// A workgroup's prologue, first tiles and records in the same units: ~10 us beside 1.4 us per 32 rows.
+constexpr int kBFixedWeight = 960;
 using BlockCut = StreamCut<kWGather, kWFull>;
 
 template <bool PAGED, bool TRAIN>
@@ -1755,10 +1757,17 @@ AttnPlan plan_attn(int S, int Hkv, int Hq, int nq, int num_views, int ld_idx, in
       pl.ws_bytes = pl.counter_bytes;
       return pl;
     }
+    // a share holds at most weight / (nW * kWFull) + 1 entries, and each of its pieces (one per branch
+    // at most) pads its last tile, as do the prefetches past the end: together within the slot table.
+    // nw_hi is the count of a table that knew neither the weights nor the branch count.
     const int64_t stream_max = (int64_t)num_views * ld_idx + (with_full ? max_L : 0);
-    int64_t nw = (kTargetBlocks + pl.units - 1) / pl.units;
-    const int64_t nw_table = stream_cut_min_workgroups<kWGather, kWFull>(stream_max, kMaxSplitKeys);
-    if (nw < nw_table) nw = nw_table;
+    const int64_t weight = (int64_t)kWGather * num_views * ld_idx + (with_full ? (int64_t)kWFull * max_L : 0);
+    const int64_t per_share = (int64_t)kWFull * (kBSlotCap - (pl.nbr + kBRing) * kTile - 1);
+    const int64_t nw_lo = (weight + per_share - 1) / per_share;
+    const int64_t per_old = (int64_t)kWFull * (kMaxSplitKeys - 32);
+    int64_t nw_hi = (kTargetBlocks + pl.units - 1) / pl.units;
+    if (nw_hi < (kWGather * stream_max + per_old - 1) / per_old) nw_hi = (kWGather * stream_max + per_old - 1) / per_old;
+    int64_t nw = plan_stream_workgroups(pl.units, nw_lo, nw_hi, weight, kBFixedWeight);
     if (nw < 1) nw = 1;
     pl.nW = (int)nw;
     const int64_t blocks = (int64_t)pl.units * nw;

@@ -58,7 +58,9 @@ constexpr int kQThreads = kQWaves * kWave;
 constexpr int kQRing = 5;                          // tile slots; kQRing-1 tiles in flight
 constexpr int kQLoads = 24;                        // 16-byte loads per lane per tile (3 per wave)
 constexpr int kQTileBytes = 16384 + kRmTileBytes; // K and V in the score layout, then K row-major
-constexpr int kQSlotCap = kMaxSplitKeys + kQRing * kTile;
+constexpr int kQMaxEntries = 4096;                 // entries of a workgroup's share: what the LDS beside the ring holds
+constexpr int kQSlotCap = kQMaxEntries + kQRing * kTile;
+constexpr int kQFixedEntries = 112;                // a workgroup's prologue and record, in entries (~10 us)
 constexpr int kRecFloats = 2 * 16 * kD;            // one wave's dQ partial: 32 rows x 128
 
 struct DqSmem {
@@ -828,12 +830,17 @@ AttnBwdPlan plan_attn_bwd(int S, int Hkv, int Hq, int C, int num_views, int ld_i
     return pl;
   }
   pl.nkt = (C + 15) / 16;
-  // workgroups per unit: enough to fill the CUs once, and enough that no range overflows the slot
-  // table (a piece's range is at most kMaxSplitKeys entries)
+  // workgroups per unit: the rounds of the CUs filled, and enough that no share overflows the slot
+  // table.  At 16K tokens, C = 256 and four views the 2,048-entry table asked for 13 per unit, 416
+  // workgroups in two rounds, the second 62% full; with 8 per unit there is one full round
+  // (training pass there 483 -> 421 us, with the forward's 16 -> 8)
   const int64_t stream_max = (int64_t)num_views * ld_idx + (with_full ? max_L : 0);
-  int64_t nw = (kTargetBlocks + pl.units - 1) / pl.units;
-  const int64_t nw_table = stream_cut_min_workgroups<kQWGather, kQWFull>(stream_max, kMaxSplitKeys);
-  if (nw < nw_table) nw = nw_table;
+  int64_t nw_hi = (kTargetBlocks + pl.units - 1) / pl.units;
+  const int64_t nw_table = (stream_max + kMaxSplitKeys - 33) / (kMaxSplitKeys - 32);
+  if (nw_hi < nw_table) nw_hi = nw_table;
+  // shares are whole tiles: a share of at most kQMaxEntries (a multiple of the tile) never overflows
+  int64_t nw = plan_stream_workgroups(pl.units, (stream_max + kQMaxEntries - 1) / kQMaxEntries, nw_hi, stream_max,
+                                      kQFixedEntries);
   if (nw < 1) nw = 1;
   pl.nW = (int)nw;
   pl.nblk_q = sat((int64_t)pl.units * nw);

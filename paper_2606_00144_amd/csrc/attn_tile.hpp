@@ -169,12 +169,29 @@ struct StreamCut {
     return x < total ? x : total;
   }
 };
-// Most entries a share can hold: chunk / WF + 1 with chunk = ceil(weighted total / nW); the
-// smallest nW keeping that within `cap` for a stream of at most stream_max entries.
-template <int WG, int WF>
-inline int64_t stream_cut_min_workgroups(int64_t stream_max, int cap) {
-  const int64_t per = (int64_t)WF * (cap - 32);
-  return (WG * stream_max + per - 1) / per;
+// Workgroups per unit for `units` streams of at most `weight` each (weighted as StreamCut weighs them),
+// between nw_lo (no share overflows its slot table) and nw_hi (the scratch planned for).  A CU holds
+// one workgroup of these kernels, so a launch of more than kCus workgroups runs in rounds, and one
+// that just exceeds a multiple leaves its last round nearly empty: 24 units at ceil(256 / 24) = 11
+// each are 264 workgroups, two rounds of a 1/11 share, where 10 each take one round of a 1/10 share
+// (3 sequences x 8 KV heads at 8K, C = 64, four views: forward 90 -> 57 us, training pass 287 -> 215 us).
+// So the count that ends first is taken: rounds x (a share + the fixed cost of a workgroup).
+constexpr int64_t kCus = 256;
+inline int64_t plan_stream_workgroups(int64_t units, int64_t nw_lo, int64_t nw_hi, int64_t weight, int64_t fixed) {
+  if (nw_lo < 1) nw_lo = 1;
+  if (nw_hi < nw_lo) nw_hi = nw_lo;
+  int64_t best = nw_lo, best_cost = INT64_MAX;
+  // only the largest counts of 1, 2, ... whole rounds can be best
+  for (int64_t r = (units * nw_lo + kCus - 1) / kCus, tries = 0; tries < 16; ++r, ++tries) {
+    int64_t nw = kCus * r / units;
+    if (nw < nw_lo) nw = nw_lo;
+    if (nw > nw_hi) nw = nw_hi;
+    const int64_t rounds = (units * nw + kCus - 1) / kCus;
+    const int64_t cost = rounds * ((weight + nw - 1) / nw + fixed);
+    if (cost < best_cost) { best_cost = cost; best = nw; }
+    if (nw == nw_hi) break;
+  }
+  return best;
 }
 
 }  // namespace bd
