@@ -28,8 +28,8 @@
 // rows (4 full rows per load instruction across the wave, fully coalesced)
 // and transposes the 8x8 bf16 block in registers with byte permutes.
 // The head dimension is contracted in a lane-group-major order (lane group
-// l/16 owns d in [32*(l/16), 32*(l/16)+32)), so each lane reads 64 contiguous
-// bytes of a key row; the order of a contraction does not change its value.
+// l/16 owns d in [32*(l/16), 32*(l/16)+32)); the order of a contraction does
+// not change its value.
 
 #include "bd_common.hpp"
 #include "bd_kernels.hpp"
@@ -75,7 +75,7 @@ struct AttnSmem {
     struct {
       alignas(16) int32_t roff[kSlotCap];
       alignas(16) int32_t tpos[kSlotCap];
-      alignas(16) uint8_t ring[kWaves][kRing][kTileBytes];   // per-wave tile slots filled by DMA
+      alignas(64) uint8_t ring[kWaves][kRing][kTileBytes];   // per-wave tile slots filled by DMA
     } slots;
     struct {
       alignas(16) float o[kWaves][16 * NT][kD + 4]; // per-wave unnormalised outputs (rows padded: the
@@ -96,121 +96,128 @@ struct TileRegs {
   u32x4 tp[2];       // positions of the 8 score slots (-1 = absent), slot i in tp[i/4][i%4]
 };
 
-// Row offsets (16-byte units) of the 10 key rows a lane loads for one tile:
-// K rows slot0+lr and slot0+16+lr, V rows slot0 + 16h + 4*(lane/16) + 0..3.
+// Row offsets (16-byte units) of the 8 key rows a lane's loads touch: load (h, i) brings row
+// slot0 + 16h + 4*(lane/16) + i, of K and of V.
 struct TileRows {
-  uint32_t k[2];
-  u32x4 v[2];
+  u32x4 r[2];
 };
+
+// Where a lane finds chunk 4*(lane/16) + j (16 bytes) of K row lane%16 of a sub-tile: row m of a
+// sub-tile was brought by load i = m%4 to byte 1024*i + 256*(m/4), its chunk c at position
+// c ^ k_swizzle(m).  All rows start on the same LDS bank and the swizzle gives the 16 rows 16
+// different positions, so the score reads meet no bank twice.
+__device__ inline uint32_t k_swizzle(int m) { return (uint32_t)(((m & 7) << 1) | (m >> 3)); }
+__device__ inline uint32_t k_lane_off(int lane) {
+  const int lg = lane >> 4, lr = lane & 15;
+  return 1024u * (uint32_t)(lr & 3) + 256u * (uint32_t)(lr >> 2) + 16u * ((uint32_t)(4 * lg) ^ k_swizzle(lr));
+}
 
 // Read a tile's row offsets from the LDS slot table: loads and their wait in one asm statement.
 __device__ inline void read_rows(TileRows& A, uint32_t roff_lds, int slot0, int lane) {
-  const int lg = lane >> 4, lr = lane & 15;
-  const uint32_t ak = roff_lds + 4 * (slot0 + lr);
-  const uint32_t av = roff_lds + 4 * (slot0 + 4 * lg);
+  const uint32_t av = roff_lds + 4 * (slot0 + 4 * (lane >> 4));
   asm volatile(
-      "ds_read_b32 %0, %4\n"
-      "ds_read_b32 %1, %4 offset:64\n"
-      "ds_read_b128 %2, %5\n"
-      "ds_read_b128 %3, %5 offset:64\n"
+      "ds_read_b128 %0, %2\n"
+      "ds_read_b128 %1, %2 offset:64\n"
       "s_waitcnt lgkmcnt(0)"
-      : "=&v"(A.k[0]), "=&v"(A.k[1]), "=&v"(A.v[0]), "=&v"(A.v[1])
-      : "v"(ak), "v"(av));
+      : "=&v"(A.r[0]), "=&v"(A.r[1])
+      : "v"(av));
 }
 
 // Copy the landed tile in LDS slot `src` into registers and read the row offsets of the
 // tile to prefetch next, all in one asm statement ending in its own wait.
 template <int NT, bool PAGED>
-__device__ inline void read_tile_and_rows(TileRegs<NT, PAGED>& T, TileRows& A, uint32_t src, uint32_t tpos_lds,
-                                          int slot0, uint32_t roff_lds, int next0, int lane) {
-  const int lg = lane >> 4, lr = lane & 15;
-  const uint32_t at = src + 16 * lane;
-  const uint32_t ap = tpos_lds + 4 * (slot0 + 4 * lg);
-  const uint32_t ak = roff_lds + 4 * (next0 + lr);
-  const uint32_t av = roff_lds + 4 * (next0 + 4 * lg);
+__device__ inline void read_tile_and_rows(TileRegs<NT, PAGED>& T, TileRows& A, uint32_t src, uint32_t koff,
+                                          uint32_t tpos_lds, int slot0, uint32_t roff_lds, int next0, int lane) {
+  const uint32_t at = src + 16 * lane, ak = src + koff;
+  const uint32_t ap = tpos_lds + 4 * (slot0 + 4 * (lane >> 4));
+  const uint32_t av = roff_lds + 4 * (next0 + 4 * (lane >> 4));
   asm volatile(
-      "ds_read_b128 %0, %22\n"
-      "ds_read_b128 %1, %22 offset:1024\n"
-      "ds_read_b128 %2, %22 offset:2048\n"
-      "ds_read_b128 %3, %22 offset:3072\n"
-      "ds_read_b128 %4, %22 offset:4096\n"
-      "ds_read_b128 %5, %22 offset:5120\n"
-      "ds_read_b128 %6, %22 offset:6144\n"
-      "ds_read_b128 %7, %22 offset:7168\n"
-      "ds_read_b128 %8, %22 offset:8192\n"
-      "ds_read_b128 %9, %22 offset:9216\n"
-      "ds_read_b128 %10, %22 offset:10240\n"
-      "ds_read_b128 %11, %22 offset:11264\n"
-      "ds_read_b128 %12, %22 offset:12288\n"
-      "ds_read_b128 %13, %22 offset:13312\n"
-      "ds_read_b128 %14, %22 offset:14336\n"
-      "ds_read_b128 %15, %22 offset:15360\n"
-      "ds_read_b128 %16, %23\n"
-      "ds_read_b128 %17, %23 offset:64\n"
-      "ds_read_b32 %18, %24\n"
-      "ds_read_b32 %19, %24 offset:64\n"
-      "ds_read_b128 %20, %25\n"
-      "ds_read_b128 %21, %25 offset:64\n"
+      "ds_read_b128 %0, %20\n"
+      "ds_read_b128 %1, %21\n"
+      "ds_read_b128 %2, %22\n"
+      "ds_read_b128 %3, %23\n"
+      "ds_read_b128 %4, %20 offset:4096\n"
+      "ds_read_b128 %5, %21 offset:4096\n"
+      "ds_read_b128 %6, %22 offset:4096\n"
+      "ds_read_b128 %7, %23 offset:4096\n"
+      "ds_read_b128 %8, %24 offset:8192\n"
+      "ds_read_b128 %9, %24 offset:9216\n"
+      "ds_read_b128 %10, %24 offset:10240\n"
+      "ds_read_b128 %11, %24 offset:11264\n"
+      "ds_read_b128 %12, %24 offset:12288\n"
+      "ds_read_b128 %13, %24 offset:13312\n"
+      "ds_read_b128 %14, %24 offset:14336\n"
+      "ds_read_b128 %15, %24 offset:15360\n"
+      "ds_read_b128 %16, %25\n"
+      "ds_read_b128 %17, %25 offset:64\n"
+      "ds_read_b128 %18, %26\n"
+      "ds_read_b128 %19, %26 offset:64\n"
       "s_waitcnt lgkmcnt(0)"
       : "=&v"(T.k[0][0]), "=&v"(T.k[0][1]), "=&v"(T.k[0][2]), "=&v"(T.k[0][3]), "=&v"(T.k[1][0]),
         "=&v"(T.k[1][1]), "=&v"(T.k[1][2]), "=&v"(T.k[1][3]), "=&v"(T.v[0]), "=&v"(T.v[1]), "=&v"(T.v[2]),
         "=&v"(T.v[3]), "=&v"(T.v[4]), "=&v"(T.v[5]), "=&v"(T.v[6]), "=&v"(T.v[7]), "=&v"(T.tp[0]), "=&v"(T.tp[1]),
-        "=&v"(A.k[0]), "=&v"(A.k[1]), "=&v"(A.v[0]), "=&v"(A.v[1])
-      : "v"(at), "v"(ap), "v"(ak), "v"(av));
+        "=&v"(A.r[0]), "=&v"(A.r[1])
+      : "v"(ak), "v"(ak ^ 16u), "v"(ak ^ 32u), "v"(ak ^ 48u), "v"(at), "v"(ap), "v"(av));
 }
 
 // Copy the landed tile in LDS slot `src` into registers (keys whose row offsets are computed).
 template <int NT, bool PAGED>
-__device__ inline void read_tile(TileRegs<NT, PAGED>& T, uint32_t src, int lane) {
-  const uint32_t at = src + 16 * lane;
+__device__ inline void read_tile(TileRegs<NT, PAGED>& T, uint32_t src, uint32_t koff, int lane) {
+  const uint32_t at = src + 16 * lane, ak = src + koff;
   asm volatile(
       "ds_read_b128 %0, %16\n"
-      "ds_read_b128 %1, %16 offset:1024\n"
-      "ds_read_b128 %2, %16 offset:2048\n"
-      "ds_read_b128 %3, %16 offset:3072\n"
+      "ds_read_b128 %1, %17\n"
+      "ds_read_b128 %2, %18\n"
+      "ds_read_b128 %3, %19\n"
       "ds_read_b128 %4, %16 offset:4096\n"
-      "ds_read_b128 %5, %16 offset:5120\n"
-      "ds_read_b128 %6, %16 offset:6144\n"
-      "ds_read_b128 %7, %16 offset:7168\n"
-      "ds_read_b128 %8, %16 offset:8192\n"
-      "ds_read_b128 %9, %16 offset:9216\n"
-      "ds_read_b128 %10, %16 offset:10240\n"
-      "ds_read_b128 %11, %16 offset:11264\n"
-      "ds_read_b128 %12, %16 offset:12288\n"
-      "ds_read_b128 %13, %16 offset:13312\n"
-      "ds_read_b128 %14, %16 offset:14336\n"
-      "ds_read_b128 %15, %16 offset:15360\n"
+      "ds_read_b128 %5, %17 offset:4096\n"
+      "ds_read_b128 %6, %18 offset:4096\n"
+      "ds_read_b128 %7, %19 offset:4096\n"
+      "ds_read_b128 %8, %20 offset:8192\n"
+      "ds_read_b128 %9, %20 offset:9216\n"
+      "ds_read_b128 %10, %20 offset:10240\n"
+      "ds_read_b128 %11, %20 offset:11264\n"
+      "ds_read_b128 %12, %20 offset:12288\n"
+      "ds_read_b128 %13, %20 offset:13312\n"
+      "ds_read_b128 %14, %20 offset:14336\n"
+      "ds_read_b128 %15, %20 offset:15360\n"
       "s_waitcnt lgkmcnt(0)"
       : "=&v"(T.k[0][0]), "=&v"(T.k[0][1]), "=&v"(T.k[0][2]), "=&v"(T.k[0][3]), "=&v"(T.k[1][0]),
         "=&v"(T.k[1][1]), "=&v"(T.k[1][2]), "=&v"(T.k[1][3]), "=&v"(T.v[0]), "=&v"(T.v[1]), "=&v"(T.v[2]),
         "=&v"(T.v[3]), "=&v"(T.v[4]), "=&v"(T.v[5]), "=&v"(T.v[6]), "=&v"(T.v[7])
-      : "v"(at));
+      : "v"(ak), "v"(ak ^ 16u), "v"(ak ^ 32u), "v"(ak ^ 48u), "v"(at));
 }
 
-// Issue the direct-to-LDS loads of a tile into `dst`: load q of a lane lands at
-// dst + q*1 KiB + 16*lane (q 0..7: K subtile q/4, k-step q%4; q 8..15: V row slot q-8).
-// Row offsets are clamped to the layout's extent (validated on the host), so no
-// value can address outside the K/V allocation.  `stream_v`: the V rows are read
-// once per call (the full branch of verify) and load non-temporally.  Measured on
-// the 16K verify: 100 -> 85 us.  Whole-line V reads gain, while the K reads, each
-// line taken in four 32-byte parts by four instructions, lose under the same
-// policy.  Gathered lists keep the default: the drafts re-read their entries.
+// Issue the direct-to-LDS loads of a tile into `dst`: load (h, i) of K lands at dst + (4h + i) KiB, of V
+// at 8 KiB past that, 16 bytes a lane.  Both bring four whole 256-byte rows, a V row's chunks in order, a
+// K row's chunks permuted (k_swizzle) so that the score operands read without bank conflicts.
+// Row offsets are clamped to the layout's extent (validated on the host), so no value can address
+// outside the K/V allocation.  `stream`: the rows are read once per call (the full branch of verify) and
+// load non-temporally.  Gathered lists keep the default: the drafts re-read their entries.
+// Whole rows matter: with each lane fetching its own 64 bytes of a key row (an instruction then touches
+// 16 rows in 16-byte parts) K needed the caches to combine four parts of a line and lost under the
+// non-temporal policy.  Measured with whole rows, K and V non-temporal: 64 ragged MHA sequences of 4K-16K
+// in 16-row pages 1617 -> 1526 us (6.5 TB/s); a captured round of 8 sequences at 16K 200 -> 189 us, as
+// verify's K no longer evicts the drafts' rows and the logits from the memory-side cache.
 __device__ inline void dma_tile(const KvView& kv, const TileRows& A, uint32_t max_roff, uint8_t* dst, int lane,
-                                bool stream_v) {
+                                bool stream) {
   const int lg = lane >> 4, lr = lane & 15;
-#pragma unroll
-  for (int sub = 0; sub < 2; ++sub) {
-    const uint32_t ro = A.k[sub] < max_roff ? A.k[sub] : max_roff;
-    const uint16_t* kr = kv.k + ((uint64_t)ro << 3) + 32 * lg;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) dma16(kr + 8 * j, dst + (4 * sub + j) * 1024);
-  }
+  const int kc = lr ^ (int)k_swizzle(4 * lg);
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const uint32_t ro = A.v[h][i] < max_roff ? A.v[h][i] : max_roff;
-      if (stream_v) dma16_nt(kv.v + ((uint64_t)ro << 3) + 8 * lr, dst + (8 + 4 * h + i) * 1024);
+      const uint32_t ro = A.r[h][i] < max_roff ? A.r[h][i] : max_roff;
+      const uint16_t* kr = kv.k + ((uint64_t)ro << 3) + 8 * (kc ^ (2 * i));   // k_swizzle(4*lg + i) = k_swizzle(4*lg) ^ 2i
+      if (stream) dma16_nt(kr, dst + (4 * h + i) * 1024);
+      else dma16(kr, dst + (4 * h + i) * 1024);
+    }
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t ro = A.r[h][i] < max_roff ? A.r[h][i] : max_roff;
+      if (stream) dma16_nt(kv.v + ((uint64_t)ro << 3) + 8 * lr, dst + (8 + 4 * h + i) * 1024);
       else dma16(kv.v + ((uint64_t)ro << 3) + 8 * lr, dst + (8 + 4 * h + i) * 1024);
     }
 }
@@ -557,6 +564,7 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p) {
     uint8_t* slot_a = sm.u.slots.ring[wave][0];
     uint8_t* slot_b = sm.u.slots.ring[wave][1];
     const uint32_t slot_a_lds = lds_addr(slot_a), slot_b_lds = lds_addr(slot_b);
+    const uint32_t koff = k_lane_off(lane);
     TileRows A;
     TileRegs<NT, PAGED> T;
     if (arith) {
@@ -565,22 +573,17 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p) {
       // dma_tile and are masked by their positions
       const uint32_t base16 = (uint32_t)(((int64_t)s * p.kv.stride_seq + (int64_t)g * p.kv.stride_head) >> 3);
       const uint32_t tok16 = (uint32_t)(p.kv.stride_tok >> 3);
-      const uint32_t off_k0 = (uint32_t)lr * tok16, off_k1 = (uint32_t)(16 + lr) * tok16;
-      const uint32_t off_v = (uint32_t)(4 * lg) * tok16;
+      const uint32_t off_r = (uint32_t)(4 * lg) * tok16;
       auto rows_at = [&](int slot0) {
         if (slot0 >= ntiles * kTile) {   // a padding tile past this wave's last: row 0, a cache-resident address
-          A.k[0] = A.k[1] = 0u;
-#pragma unroll
-          for (int h = 0; h < 2; ++h) A.v[h] = u32x4{0u, 0u, 0u, 0u};
+          A.r[0] = A.r[1] = u32x4{0u, 0u, 0u, 0u};
           return;
         }
         const uint32_t r0 = base16 + (uint32_t)(e_begin + slot0) * tok16;
-        A.k[0] = r0 + off_k0;
-        A.k[1] = r0 + off_k1;
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) A.v[h][i] = r0 + (uint32_t)(16 * h + i) * tok16 + off_v;
+          for (int i = 0; i < 4; ++i) A.r[h][i] = r0 + (uint32_t)(16 * h + i) * tok16 + off_r;
       };
       auto pos_at = [&](int slot0) {
         return [=](int i) {
@@ -594,13 +597,13 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p) {
       dma_tile(p.kv, A, p.max_roff, slot_b, lane, !gather);
       for (int it = wave;; it += 2 * kWaves) {
         asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-        read_tile<NT, PAGED>(T, slot_a_lds, lane);
+        read_tile<NT, PAGED>(T, slot_a_lds, koff, lane);
         rows_at(kTile * (it + 2 * kWaves));
         dma_tile(p.kv, A, p.max_roff, slot_a, lane, !gather);
         tile_step<NT, PAGED>(st, T, qop, rowpos, p.scale_log2, it >= first_dirty, want_lx, pos_at(kTile * it), pass_v(T));
         if (it + kWaves >= ntiles) break;
         asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-        read_tile<NT, PAGED>(T, slot_b_lds, lane);
+        read_tile<NT, PAGED>(T, slot_b_lds, koff, lane);
         rows_at(kTile * (it + 3 * kWaves));
         dma_tile(p.kv, A, p.max_roff, slot_b, lane, !gather);
         tile_step<NT, PAGED>(st, T, qop, rowpos, p.scale_log2, it + kWaves >= first_dirty, want_lx,
@@ -614,13 +617,11 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p) {
       const uint32_t roff_lds = lds_addr(sm.u.slots.roff);
       const uint32_t tok16 = (uint32_t)(p.kv.stride_tok >> 3);
       const int P = p.kv.page_size;
-      const uint32_t off_k = (uint32_t)lr, off_v = (uint32_t)(4 * lg);
+      const uint32_t off_r = (uint32_t)(4 * lg);
       auto rows_at = [&](int slot0, uint32_t& vb) {
         vb = 0u;
         if (slot0 >= ntiles * kTile) {   // a padding tile past this wave's last: row 0, a cache-resident address
-          A.k[0] = A.k[1] = 0u;
-#pragma unroll
-          for (int h = 0; h < 2; ++h) A.v[h] = u32x4{0u, 0u, 0u, 0u};
+          A.r[0] = A.r[1] = u32x4{0u, 0u, 0u, 0u};
           return;
         }
         uint32_t a[2], w[2];
@@ -645,9 +646,8 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p) {
           const bool ok = b[h] != 0xFFFFFFFFu;
           vb |= ok ? (1u << h) : 0u;
           const uint32_t base = ok ? b[h] : 0u;
-          A.k[h] = base + (w[h] + off_k) * tok16;
 #pragma unroll
-          for (int i = 0; i < 4; ++i) A.v[h][i] = base + (w[h] + off_v + (uint32_t)i) * tok16;
+          for (int i = 0; i < 4; ++i) A.r[h][i] = base + (w[h] + off_r + (uint32_t)i) * tok16;
         }
       };
       auto pos_at = [&](int slot0, uint32_t vb) {
@@ -663,7 +663,7 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p) {
       dma_tile(p.kv, A, p.max_roff, slot_b, lane, true);
       for (int it = wave;; it += 2 * kWaves) {
         asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-        read_tile<NT, PAGED>(T, slot_a_lds, lane);
+        read_tile<NT, PAGED>(T, slot_a_lds, koff, lane);
         const uint32_t vb_now = vb_a;
         rows_at(kTile * (it + 2 * kWaves), vb_a);
         dma_tile(p.kv, A, p.max_roff, slot_a, lane, true);
@@ -671,7 +671,7 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p) {
                              pass_v(T));
         if (it + kWaves >= ntiles) break;
         asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-        read_tile<NT, PAGED>(T, slot_b_lds, lane);
+        read_tile<NT, PAGED>(T, slot_b_lds, koff, lane);
         const uint32_t vb_next = vb_b;
         rows_at(kTile * (it + 3 * kWaves), vb_b);
         dma_tile(p.kv, A, p.max_roff, slot_b, lane, true);
@@ -689,13 +689,13 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p) {
       dma_tile(p.kv, A, p.max_roff, slot_b, lane, !gather);
       for (int it = wave;; it += 2 * kWaves) {
         asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-        read_tile_and_rows<NT, PAGED>(T, A, slot_a_lds, tpos_lds, kTile * it, roff_lds, kTile * (it + 2 * kWaves),
+        read_tile_and_rows<NT, PAGED>(T, A, slot_a_lds, koff, tpos_lds, kTile * it, roff_lds, kTile * (it + 2 * kWaves),
                                       lane);
         dma_tile(p.kv, A, p.max_roff, slot_a, lane, !gather);
         tile_step<NT, PAGED>(st, T, qop, rowpos, p.scale_log2, it >= first_dirty, want_lx, pos_of, pass_v(T));
         if (it + kWaves >= ntiles) break;
         asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-        read_tile_and_rows<NT, PAGED>(T, A, slot_b_lds, tpos_lds, kTile * (it + kWaves), roff_lds,
+        read_tile_and_rows<NT, PAGED>(T, A, slot_b_lds, koff, tpos_lds, kTile * (it + kWaves), roff_lds,
                                       kTile * (it + 3 * kWaves), lane);
         dma_tile(p.kv, A, p.max_roff, slot_b, lane, !gather);
         tile_step<NT, PAGED>(st, T, qop, rowpos, p.scale_log2, it + kWaves >= first_dirty, want_lx, pos_of, pass_v(T));
