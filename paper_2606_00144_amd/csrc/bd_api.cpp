@@ -231,7 +231,10 @@ size_t bd_select_kv_workspace_bytes(int32_t num_seqs, int32_t num_kv_heads, int3
   if (!shape_ok(num_seqs, num_kv_heads, num_q_heads) || window < 1 || max_seq_len < 0) return 0;
   if ((int64_t)max_seq_len - window > BD_SELECT_MAX_PREFIX || (int64_t)window * (num_q_heads / num_kv_heads) > 4096)
     return 0;
-  return bd::plan_select(num_seqs, num_kv_heads, num_q_heads, window, max_seq_len, true).ws_bytes;
+  // over the layouts: a paged cache through the per-key table, or any other
+  const size_t a = bd::plan_select(num_seqs, num_kv_heads, num_q_heads, window, max_seq_len, true).ws_bytes;
+  const size_t b = bd::plan_select(num_seqs, num_kv_heads, num_q_heads, window, max_seq_len, false).ws_bytes;
+  return a > b ? a : b;
 }
 
 namespace {

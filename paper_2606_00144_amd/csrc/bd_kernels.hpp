@@ -29,7 +29,7 @@ struct AttnParams {
   int32_t S, Hkv, Hq, G;
   int32_t nq;               // query rows per head (1, gamma+1 or C)
   int32_t R;                // rows per (s, g): nq * G
-  int32_t n_rb;             // row blocks of 16*NT rows
+  int32_t n_rb;             // row blocks of at most 128 rows
   int32_t n_rg;             // block mode: row groups of 8 row blocks (otherwise n_rb)
   int32_t nsplit_g, kps_g;  // gathered units: splits and entries per split
   int32_t nsplit_f, kps_f;  // full units: splits and keys per split
@@ -155,7 +155,7 @@ struct SelectParams {
   int32_t keep;             // prefix positions the budget pays for: budget - W, or budget (B excludes the window)
   int32_t ld;               // index slots per (s, g): keep + W
   int32_t R;                // rows per (s, g): W * G
-  int32_t n_rb;             // row blocks of 16*NT rows
+  int32_t n_rb;             // row blocks of at most 128 rows
   int32_t nsplit, kps;      // key splits of the scoring passes
   int32_t max_L;
   float scale_log2;
@@ -176,8 +176,8 @@ struct SelectPlan {
 
 // `paged`: the cache is paged; its splits then go through a table of bounded size, with one entry per
 // key, or with `page_size` a multiple of 16 (pages hold whole 16-key sub-tiles) one per page.
-// Workspace queries that do not know the layout use paged = true with the per-key table, which has
-// at least as many splits.
+// Workspace queries that do not know the layout take the larger of the per-key table's plan and the
+// contiguous cache's (a table of pages does not bound a split of at most BD_SELECT_MAX_PREFIX + window keys).
 SelectPlan plan_select(int S, int Hkv, int Hq, int W, int max_L, bool paged, int page_size = 0);
 hipError_t launch_select(const SelectParams& p, bool paged, hipStream_t stream);
 

@@ -17,10 +17,11 @@
 //      appended.
 //
 // The scoring product is a real dense contraction ((W*G) x 128 x L per
-// (s, g)), so it runs on MFMA with the attention kernel's orientation: keys on
-// the M side, observation rows on the N side.  Lane l then holds 4 keys of
-// row l%16: row statistics stay lane-local, and a key's column sum is a
-// 16-lane DPP reduction.
+// (s, g)), so it runs on MFMA (v_mfma_f32_32x32x16_bf16) with keys on the M side
+// and observation rows on the N side: D element (8*(i/4) + 4*(l/32) + i%4, l%32)
+// sits in lane l, register i.  Lane l then holds 16 keys of row l%32: row
+// statistics stay lane-local, and a key's column sum is a reduction over the
+// 32 lanes of its half.
 
 #include <type_traits>
 
@@ -32,13 +33,13 @@ namespace {
 
 constexpr int kWaves = 8;                        // two per SIMD: one wave's MFMA and loads overlap another's VALU
 constexpr int kThreads = kWaves * kWave;
-constexpr int kTile = 32;                        // keys per wave iteration (two MFMA sub-tiles of 16)
+constexpr int kTile = 32;                        // keys per wave iteration
 constexpr int kTileLoads = 8;                    // 16-byte loads per lane per tile
 constexpr int kTileBytes = kTileLoads * kWave * 16;
 constexpr int kRing = 2;                         // tile slots per wave: one in flight while one is computed
 constexpr int kMaxPagedKeys = 4096;              // keys per workgroup through the paged slot table
 constexpr int kSlotCap = kMaxPagedKeys + kRing * kWaves * kTile;
-constexpr int kStatRows = 128;                   // stats record stride (rows)
+constexpr int kStatRows = 128;                   // stats record stride (rows); the most rows of a block
 constexpr int kTargetBlocks = 256;               // one workgroup per CU
 constexpr int kTopkThreads = 1024;
 constexpr int kMaxPerThread = BD_SELECT_MAX_PREFIX / kTopkThreads;   // 32
@@ -49,7 +50,8 @@ __device__ inline int digit_bits(int i) { return i == 0 ? 8 : (i == 1 ? 11 : 12)
 __device__ inline int digit_shift(int i) { return i == 0 ? 23 : (i == 1 ? 12 : 0); }
 __device__ inline int digit_copies(int i) { return i == 0 ? 16 : (i == 1 ? 2 : 1); }
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kSlack = 8.f;                    // lazy-rescale headroom of the pass-1 sums, log2 units
+constexpr float kRaiseSum = 4096.f;              // pass 1: a lane's 16 weights of a row may sum to this before its reference is raised
+constexpr float kNoRef = -3.0e38f;               // pass 1: reference of a row that has seen no key
 
 __device__ inline void merge_ml(float& m, float& l, float m2, float l2) {
   const float M = fmaxf(m, m2);
@@ -73,73 +75,149 @@ __device__ inline int fetch_select_args(const SelectParams& p) {
   return z2;
 }
 
-template <int NT, bool PAGED>
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+template <int RT, bool PAGED>
 struct ScoreSmem {
-  alignas(16) uint8_t ring[kWaves][kRing][kTileBytes];   // per-wave K tile slots filled by DMA
+  alignas(64) uint8_t ring[kWaves][kRing][kTileBytes];   // per-wave K tile slots filled by DMA
   alignas(16) int32_t roff[PAGED ? kSlotCap : 4];        // paged: row offset (16-byte units) per key slot
-  float m[kWaves][16 * NT];
-  float l[kWaves][16 * NT];
-  float lse2[16 * NT];
+  float m[kWaves][32 * RT];
+  float l[kWaves][32 * RT];
+  float lse2[32 * RT];
 };
 
-__device__ inline void dma16(const uint16_t* g, uint8_t* l) {
-  __builtin_amdgcn_global_load_lds((const void*)g, (__attribute__((address_space(3))) void*)l, 16, 0, 0);
+// One 16-byte direct-to-LDS load: lane l's bytes land at LDS address `dst` + 16*l.  Issued by hand so that
+// the compiler's wait analysis does not see it: it would otherwise wait for every such load in flight
+// before any LDS read.  The waits are explicit (vmcnt before a tile is read).  M0 is a reserved register:
+// the compiler keeps nothing in it, and nothing else in these kernels uses it.
+__device__ inline void dma16(const uint16_t* g, uint32_t dst) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n"
+      "s_nop 0\n"
+      "global_load_lds_dwordx4 %1, off"
+      :
+      : "s"(dst), "v"(g)
+      : "memory");
 }
 
-// Direct-to-LDS loads of one K tile: load q (sub-tile q/4, k-step q%4) of a lane lands at
-// dst + q*1 KiB + 16*lane; the lane's rows are r[sub] (16-byte units, clamped to the layout).
-__device__ inline void dma_ktile(const uint16_t* k, const uint32_t (&r)[2], uint32_t max_roff, uint8_t* dst, int lane) {
-  const int lg = lane >> 4;
+// Direct-to-LDS loads of one K tile: load (h, i) brings the four whole rows 16h + 4*(lane/16) + i to
+// dst + (4h + i) KiB, 16 bytes a lane; r[h][i] are the lane's rows (16-byte units, clamped to the
+// layout).  Chunk c (16 bytes) of row m lands at position c ^ k_swizzle(m % 16) of its 256 bytes: all
+// rows start on the same LDS bank, and the swizzle puts the rows of a score read on different ones.
+__device__ inline int k_swizzle(int m) { return ((m & 7) << 1) | (m >> 3); }
+__device__ inline void dma_ktile(const uint16_t* k, const u32x4 (&r)[2], uint32_t max_roff, uint32_t dst, int lane) {
+  const int kc = (lane & 15) ^ k_swizzle(4 * (lane >> 4));
 #pragma unroll
-  for (int sub = 0; sub < 2; ++sub) {
-    const uint32_t ro = r[sub] < max_roff ? r[sub] : max_roff;
-    const uint16_t* kr = k + ((uint64_t)ro << 3) + 32 * lg;
+  for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) dma16(kr + 8 * j, dst + (4 * sub + j) * 1024);
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t ro = r[h][i] < max_roff ? r[h][i] : max_roff;
+      dma16(k + ((uint64_t)ro << 3) + 8 * (kc ^ (2 * i)), dst + (4 * h + i) * 1024);   // swizzle of row 4*lg + i
+    }
+}
+// Byte offset in a tile of chunk 8*(lane/32) of row lane%32; chunk + j is at this ^ 16*j.
+__device__ inline uint32_t k_lane_off(int lane) {
+  const int m = lane & 31;
+  return 4096u * (uint32_t)(m >> 4) + 1024u * (uint32_t)(m & 3) + 256u * (uint32_t)((m >> 2) & 3) +
+         16u * (uint32_t)((8 * (lane >> 5)) ^ k_swizzle(m & 15));
+}
+
+// The same for a tile whose two 16-key sub-tiles are runs of rows `stride` bytes apart, from uniform byte
+// offsets base[h] into K: the address of a load is a scalar base plus a lane-constant offset, so a tile
+// costs few vector instructions.  The caller knows that all 32 rows lie in the layout.
+__device__ inline void dma16_run(const uint16_t* base, uint32_t voff, uint32_t dst) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n"
+      "s_nop 0\n"
+      "global_load_lds_dwordx4 %1, %2"
+      :
+      : "s"(dst), "v"(voff), "s"(base)
+      : "memory");
+}
+__device__ inline void dma_krun(const uint16_t* k, const uint64_t (&base)[2], uint32_t stride, uint32_t dst) {
+  // the lane offsets are formed again for each tile, from the lane index up: kept across the loop they
+  // cost spills, and a reload waits for every load in flight
+  int lane;
+  asm volatile(
+      "v_mbcnt_lo_u32_b32 %0, -1, 0\n"
+      "v_mbcnt_hi_u32_b32 %0, -1, %0"
+      : "=&v"(lane));
+  const uint32_t voff_row = (uint32_t)(4 * (lane >> 4)) * stride;
+  const uint32_t voff_chunk = 16u * (uint32_t)((lane & 15) ^ k_swizzle(4 * (lane >> 4)));
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t voff = voff_row + (voff_chunk ^ (32u * (uint32_t)i));
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      dma16_run(reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(k) + base[h] + (uint64_t)((uint32_t)i * stride)),
+                voff, dst + (4 * h + i) * 1024);
   }
 }
 
-// Copy a landed K tile into registers (loads and their wait in one asm statement: the compiler
-// would otherwise wait for every direct-to-LDS load in flight before any LDS read).
-__device__ inline void read_ktile(u32x4 (&t)[2][4], uint32_t src, int lane) {
-  const uint32_t a = src + 16 * lane;
+// Row offsets of a paged tile's lane rows from the slot table (loads and their wait in one statement).
+__device__ inline void read_krows(u32x4 (&r)[2], uint32_t roff_lds, int slot0, int lane) {
+  const uint32_t a = roff_lds + 4 * (slot0 + 4 * (lane >> 4));
   asm volatile(
-      "ds_read_b128 %0, %8\n"
-      "ds_read_b128 %1, %8 offset:1024\n"
-      "ds_read_b128 %2, %8 offset:2048\n"
-      "ds_read_b128 %3, %8 offset:3072\n"
-      "ds_read_b128 %4, %8 offset:4096\n"
-      "ds_read_b128 %5, %8 offset:5120\n"
-      "ds_read_b128 %6, %8 offset:6144\n"
-      "ds_read_b128 %7, %8 offset:7168\n"
-      "s_waitcnt lgkmcnt(0)"
-      : "=&v"(t[0][0]), "=&v"(t[0][1]), "=&v"(t[0][2]), "=&v"(t[0][3]), "=&v"(t[1][0]), "=&v"(t[1][1]),
-        "=&v"(t[1][2]), "=&v"(t[1][3])
-      : "v"(a));
-}
-
-// Row offsets of a paged tile's two lane rows from the slot table.
-__device__ inline void read_krows(uint32_t (&r)[2], uint32_t roff_lds, int slot0, int lane) {
-  const uint32_t a = roff_lds + 4 * (slot0 + (lane & 15));
-  asm volatile(
-      "ds_read_b32 %0, %2\n"
-      "ds_read_b32 %1, %2 offset:64\n"
+      "ds_read_b128 %0, %2\n"
+      "ds_read_b128 %1, %2 offset:64\n"
       "s_waitcnt lgkmcnt(0)"
       : "=&v"(r[0]), "=&v"(r[1])
       : "v"(a));
 }
 
-// One pass over the causal key range of (sequence, KV head, row block, split).  Each wave streams
-// every kWaves-th 32-key tile through a kRing-deep ring of LDS slots.
+// Sums of 16 values over the 32 lanes of each half: value i of the result's key order ends in lanes with
+// l%16 == i (both rows of the half hold different values, see below).  Each step halves the values a lane
+// carries and doubles the lanes summed.  Step 1 pairs value i with value i + 8 over lanes 16 apart (one
+// permlane16_swap serves both), the others exchange within a row of 16.
+// Returns the sum that this lane ends up with; its value index is half_sum_index(lane).
+__device__ inline float half_sums(const float (&v)[16], int lane) {
+  float a[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 8]), false, false);
+    a[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);      // even rows: value i, odd rows: value i + 8
+  }
+  const bool b8 = lane & 8, b4 = lane & 4, b2 = lane & 2;
+  float c[4], d[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {      // lanes l and l ^ 8 (a rotation by 8 of the row)
+    const float keep = b8 ? a[i + 4] : a[i], give = b8 ? a[i] : a[i + 4];
+    c[i] = keep + __builtin_amdgcn_update_dpp(0.0f, give, 0x128, 0xF, 0xF, false);   // row_ror:8
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {      // the mirrored half row holds lane l ^ 7: bit 2 differs
+    const float keep = b4 ? c[i + 2] : c[i], give = b4 ? c[i] : c[i + 2];
+    d[i] = keep + __builtin_amdgcn_update_dpp(0.0f, give, 0x141, 0xF, 0xF, false);   // row_half_mirror
+  }
+  const float keep = b2 ? d[1] : d[0], give = b2 ? d[0] : d[1];
+  float e = keep + __builtin_amdgcn_update_dpp(0.0f, give, 0x4E, 0xF, 0xF, false);   // quad_perm [2,3,0,1]
+  e += __builtin_amdgcn_update_dpp(0.0f, e, 0xB1, 0xF, 0xF, false);                  // quad_perm [1,0,3,2]
+  return e;
+}
+__device__ inline int half_sum_index(int lane) {
+  return ((lane & 16) >> 1) | ((lane & 8) >> 1) | ((lane & 4) >> 1) | ((lane & 2) >> 1);
+}
+
+// One pass over the causal key range of (sequence, KV head, row block of 32*RT rows, split).  Each wave
+// streams every kWaves-th 32-key tile through a kRing-deep ring of LDS slots.
 //   PASS 1: per observation row, running max and sum of exp of the scaled logits;
 //   PASS 2: every key's column sum of the rows' normalised weights (complete within the row
 //           block: one plain store per key).
-template <int NT, bool PAGED, int PASS>
+// Per 32 x 32 scores a wave needs 8 products (32 cycles each) and 48 vector instructions (16 of them
+// exponentials at 8 cycles): the two units have equal work, so the tile loop is pipelined by row tile,
+// products of one beside the exponentials of the one before.  What bounds it: the two units at half of
+// their rates each in the loop (2.0 us per tile and wave pair), and for 128 rows at 16K x 8 the K stream.
+// Measured, 16K keys, passes 1 and 2: 8 sequences, 128 rows 58 + 51 -> 46 + 44.5 us; one sequence, 1,024
+// rows (8 blocks, K from the caches) 57.5 + 50.5 -> 43.5 + 43 us; at 4K, 128 workgroups 14.4 + 12.4 ->
+// 10.6 + 8.3 us.  Before: 16x16x32 products with all of a tile's products ahead of its exponentials, row
+// maxima for every tile, and the rows read by every wave from memory.
+template <int RT, bool PAGED, int PASS>
 __global__ __launch_bounds__(kThreads) void score_kernel(SelectParams p) {
-  __shared__ ScoreSmem<NT, PAGED> sm;
+  __shared__ ScoreSmem<RT, PAGED> sm;
+  constexpr int kRows = 32 * RT;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lg = lane >> 4, lr = lane & 15;
+  const int lg = lane >> 4, lr = lane & 31, hf = lane >> 5;
   const int bid = xcd_remap(blockIdx.x + fetch_select_args(p), gridDim.x);
   const int rb = bid % p.n_rb;
   const int rest = bid / p.n_rb;
@@ -152,21 +230,7 @@ __global__ __launch_bounds__(kThreads) void score_kernel(SelectParams p) {
   int k1 = k0 + p.kps;
   if (k1 > L) k1 = L;
   const int64_t stat_base = (((int64_t)pair * p.n_rb + rb) * p.nsplit) * kStatRows * 2;
-
-  // observation rows of this lane: n = rb*16*NT + 16*nt + lane%16 -> (window row i, head h)
-  bf16x8 qop[NT][4];
-  int rowpos[NT];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) {
-    const int n = rb * 16 * NT + 16 * nt + lr;
-    const bool valid = n < p.R;
-    const int i = valid ? n / p.G : 0;
-    const int h = g * p.G + (valid ? n % p.G : 0);
-    rowpos[nt] = valid ? L - p.W + i : -1;          // padded rows see no key
-    const uint16_t* qrow = p.q_win + (((int64_t)s * p.W + i) * p.Hq + h) * kD + 32 * lg;
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk) qop[nt][kk] = as_bf16x8(valid ? load16(qrow + 8 * kk) : u32x4{0u, 0u, 0u, 0u});
-  }
+  if (PASS == 2 && k1 <= k0) return;       // a split past this sequence's end: no key to score
 
   const int ntiles = k1 > k0 ? (k1 - k0 + kTile - 1) / kTile : 0;
   // pages holding whole 16-key sub-tiles (page_size a multiple of 16, host-checked): a table of page
@@ -176,6 +240,96 @@ __global__ __launch_bounds__(kThreads) void score_kernel(SelectParams p) {
   const int psub = PAGED ? p.kv.page_size >> 4 : 1;
   const float inv_psub = __builtin_amdgcn_rcpf((float)psub);
   const int page0 = page_arith ? div_small(k0 >> 4, psub, inv_psub) : 0;
+  const uint32_t ring_lds = lds_addr(sm.ring[wave][0]);
+  const uint32_t roff_lds = lds_addr(sm.roff);
+  const uint64_t row0 = PAGED ? 0 : (uint64_t)((int64_t)s * p.kv.stride_seq + (int64_t)g * p.kv.stride_head);
+  const uint32_t base16 = (uint32_t)(row0 >> 3), tok16 = (uint32_t)(p.kv.stride_tok >> 3);
+  const bool runs = p.kv.stride_tok <= (1 << 26);          // a run's lane offsets fit 32 bits
+  // pass 2 takes its tiles last first: pass 1 read them first to last, so the most recent (still in
+  // the memory-side cache) are read before the lines pass 1 read first are replaced
+  auto real = [&](int it) { return PASS == 2 ? ntiles - 1 - it : it; };
+  auto issue = [&](int tile, int slot) {
+    const uint32_t dst = ring_lds + slot * kTileBytes;
+    u32x4 r[2];
+    if (tile >= ntiles) {
+      r[0] = r[1] = u32x4{0u, 0u, 0u, 0u};   // padding: row 0, a safe, cache-resident address
+    } else {
+      const int tb = k0 + kTile * real(tile);
+      if constexpr (PAGED) {
+        if (page_arith) {
+          // sub-tile h (keys tb+16h .. +15) lies in one page: its offset + (key mod page_size) rows
+          uint32_t a[2], w[2], b[2];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int t = tb + 16 * h;
+            const int pi = div_small(t >> 4, psub, inv_psub);
+            a[h] = roff_lds + 4 * (uint32_t)(t < k1 ? pi - page0 : 0);   // past the split: entry 0, masked
+            w[h] = (uint32_t)(t - pi * p.kv.page_size);
+          }
+          asm volatile(
+              "ds_read_b32 %0, %2\n"
+              "ds_read_b32 %1, %3\n"
+              "s_waitcnt lgkmcnt(0)"
+              : "=&v"(b[0]), "=&v"(b[1])
+              : "v"(a[0]), "v"(a[1]));
+          if (runs) {
+            uint64_t base[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+              base[h] = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(b[h]) +
+                         (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(w[h]) * tok16) << 4;
+            dma_krun(p.kv.k, base, tok16 << 4, dst);
+            return;
+          }
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) r[h][i] = b[h] + (w[h] + (uint32_t)(4 * lg + i)) * tok16;
+        } else {
+          read_krows(r, roff_lds, kTile * real(tile), lane);
+        }
+      } else {
+        if (runs && tb + kTile <= k1) {        // whole tiles lie in the cache
+          uint64_t base[2];
+#pragma unroll
+          for (int h = 0; h < 2; ++h) base[h] = (row0 + (uint64_t)(tb + 16 * h) * (uint64_t)p.kv.stride_tok) << 1;
+          dma_krun(p.kv.k, base, tok16 << 4, dst);
+          return;
+        }
+        const uint32_t r0 = base16 + (uint32_t)(tb + 4 * lg) * tok16;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) r[h][i] = r0 + (uint32_t)(16 * h + i) * tok16;
+      }
+    }
+    dma_ktile(p.kv.k, r, p.max_roff, dst, lane);
+  };
+
+  // a contiguous cache's first tile needs only the length: it loads beside the rows
+  if (!PAGED && wave < ntiles) issue(wave, 0);
+
+  // observation rows n = rb*kRows + 32*t + lane%32 -> (window row i, head h).  All waves need them all: each
+  // brings its 4*RT rows to LDS whole (its second tile slot), chunks swizzled as a K tile's.  Read straight
+  // from memory, every wave touched a line per lane and load, 4 lines a row each, and the row loads alone
+  // took several microseconds of the CU's address path.
+  {
+    const uint32_t dst = lds_addr(sm.ring[wave][1]);
+#pragma unroll
+    for (int q = 0; q < RT; ++q) {
+      const int r = 4 * RT * wave + 4 * q + lg;
+      const int n = rb * kRows + r < p.R ? rb * kRows + r : p.R - 1;     // rows past R are dropped when read
+      const int i = n / p.G, h = g * p.G + n - i * p.G;
+      dma16(p.q_win + (((int64_t)s * p.W + i) * p.Hq + h) * kD + 8 * ((lane & 15) ^ k_swizzle(r & 15)), dst + q * 1024);
+    }
+  }
+  int rowpos[RT];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    const int n = rb * kRows + 32 * t + lr;
+    rowpos[t] = n < p.R ? L - p.W + n / p.G : -1;   // padded rows see no key
+  }
+
   if (page_arith) {
     // entry j: offset (16-byte units) of page page0 + j for head g, 0 for a page outside the pool (its
     // keys read pool rows and score as whatever those hold); all page-table loads issued first
@@ -222,22 +376,28 @@ __global__ __launch_bounds__(kThreads) void score_kernel(SelectParams p) {
 
   // lse of each row (pass 2): the caller's, or merged from the pass-1 statistics.  Padded rows get
   // +inf, so their weights are exactly zero even where no mask is applied.
-  // pass 1 per row: reference mu (log2 units, 0 until the first visible key), sum rl of exp2 relative
-  // to it, and the raw (unscaled) logit above which mu is raised
-  float rm[NT], rl[NT], rthr[NT], lse2[NT];
+  // pass 1 per row: reference mu (log2 units) and this lane's sum rl of exp2 relative to it
+  float rm[RT], rl[RT], lse2[RT];
   if constexpr (PASS == 2) {
-    if (tid < 16 * NT) {
-      const int n = rb * 16 * NT + tid;
+    if (tid < kRows) {
+      const int n = rb * kRows + tid;
       float v = INFINITY;
       if (n < p.R) {
         if (p.lse_win) {
           const int i = n / p.G, h = g * p.G + n % p.G;
           v = p.lse_win[((int64_t)s * p.W + i) * p.Hq + h] * kLog2e;
         } else {
+          // the splits merge in order; a batch of records is loaded before the first is used
+          constexpr int kBatch = 8;
           float m = -INFINITY, l = 0.f;
-          for (int sp = 0; sp < p.nsplit; ++sp) {
-            const float* st = p.stats + stat_base + ((int64_t)sp * kStatRows + tid) * 2;
-            merge_ml(m, l, st[0], st[1]);
+          const float2* st = reinterpret_cast<const float2*>(p.stats + stat_base) + tid;
+          for (int sp0 = 0; sp0 < p.nsplit; sp0 += kBatch) {
+            float2 x[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) x[u] = st[(int64_t)(sp0 + u < p.nsplit ? sp0 + u : sp0) * kStatRows];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u)
+              if (sp0 + u < p.nsplit) merge_ml(m, l, x[u].x, x[u].y);
           }
           v = l > 0.f ? m + __log2f(l) : INFINITY;   // empty row contributes nothing
         }
@@ -246,17 +406,33 @@ __global__ __launch_bounds__(kThreads) void score_kernel(SelectParams p) {
     }
   } else {
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) { rm[nt] = 0.f; rl[nt] = 0.f; rthr[nt] = -INFINITY; }
+    for (int t = 0; t < RT; ++t) { rm[t] = kNoRef; rl[t] = 0.f; }
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's rows (and first tile) are in LDS
   __syncthreads();
+  // lane half hf holds the head dimension's half hf, in 8 steps of 8 (the order of a contraction does not
+  // matter)
+  bf16x8 qop[RT][8];
+#pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    const int r = 32 * t + lr, w = r / (4 * RT), rw = r - w * (4 * RT);
+    const bool valid = rb * kRows + r < p.R;
+    const uint8_t* row = sm.ring[w][1] + 256 * rw;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const u32x4 x = *reinterpret_cast<const u32x4*>(row + 16 * ((8 * hf + j) ^ k_swizzle(r & 15)));
+      qop[t][j] = as_bf16x8(valid ? x : u32x4{0u, 0u, 0u, 0u});
+    }
+  }
   if constexpr (PASS == 2) {
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) lse2[nt] = sm.lse2[16 * nt + lr];
+    for (int t = 0; t < RT; ++t) lse2[t] = sm.lse2[32 * t + lr];
   }
+  __syncthreads();                         // every wave has the rows: the second slots take tiles
 
   // tiles whose keys all lie inside the split and at or before the block's earliest row position
   // need no mask
-  const int minpos = L - p.W + (rb * 16 * NT) / p.G;
+  const int minpos = L - p.W + (rb * kRows) / p.G;
   int first_dirty;
   {
     const int c1 = minpos - k0 - (kTile - 1);
@@ -267,196 +443,186 @@ __global__ __launch_bounds__(kThreads) void score_kernel(SelectParams p) {
 
   float* raw_part = p.raw_part + ((int64_t)pair * p.n_rb + rb) * p.max_L;
 
-  // Scores of one 16-key sub-tile against the 16*NT rows; keys tb .. tb+3 belong to this lane.
-  auto sub_products = [&](f32x4 (&acc)[NT], const u32x4 (&kr)[4]) {
+  bf16x8 kt[8];                            // the tile's keys: row lane%32, half hf of the head dimension
+  // scores of the tile against row tile t
+  auto products = [&](f32x16& acc, int t) {
+    f32x16 a;
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      f32x4 a = {0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < 16; ++i) a[i] = 0.f;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kr[j]), qop[nt][j], a, 0, 0, 0);
-      acc[nt] = a;
+    for (int j = 0; j < 8; ++j) a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt[j], qop[t][j], a, 0, 0, 0);
+    acc = a;
+  };
+  // Causal and split mask.  Only tiles that can hold a masked key call it: a mask behind a runtime flag
+  // was if-converted, and every tile paid it.  `tb`: the tile's first key.
+  auto mask = [&](f32x16& acc, int t, int tb) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int key = tb + 8 * (i >> 2) + 4 * hf + (i & 3);
+      if (!(key < k1 && key <= rowpos[t])) acc[i] = -INFINITY;
     }
   };
-  // Causal and split mask of a sub-tile.  Only tiles that can hold a masked key call it: a mask
-  // behind a runtime flag was if-converted, and every tile paid it (a compare, a select and a mask
-  // merge per score: a third of the loop's VALU instructions).
-  auto sub_mask = [&](f32x4 (&acc)[NT], int tb) {
+  // Pass 1: this lane's 16 weights of row tile t, relative to the row's reference, join its sum.  The
+  // reference is raised when they sum to more than kRaiseSum (an overflow included): the maximum over the
+  // row's keys of the tile becomes the reference, and the weights are formed again.  No maximum is taken
+  // in the common case, and rows start at a reference below every logit, so their first key raises it.
+  auto pass1_sum = [&](const f32x16& acc, int t) {
+    auto weights = [&]() {
+      float x[4];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
+      for (int i = 0; i < 4; ++i) x[i] = __builtin_amdgcn_exp2f(fmaf(acc[i], p.scale_log2, -rm[t]));
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int t = tb + i;
-        if (!(t < k1 && t <= rowpos[nt])) acc[nt][i] = -INFINITY;
+      for (int i = 4; i < 16; ++i) x[i & 3] += __builtin_amdgcn_exp2f(fmaf(acc[i], p.scale_log2, -rm[t]));
+      return (x[0] + x[1]) + (x[2] + x[3]);
+    };
+    float w = weights();
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(w > kRaiseSum) != 0, 0)) {
+      float m = acc[0];
+#pragma unroll
+      for (int i = 1; i < 16; ++i) m = fmaxf(m, acc[i]);
+      m = max_xor32(m) * p.scale_log2;     // both halves of the row; scale > 0: the max commutes with it
+      if (m > rm[t]) {
+        rl[t] *= __builtin_amdgcn_exp2f(rm[t] - m);
+        rm[t] = m;
       }
+      w = weights();
+    }
+    rl[t] += w;
   };
-
-  // Pass 1 over a 32-key tile: per-lane running sums with a lazily raised reference, so weights stay
-  // <= 2^kSlack.  Both sub-tiles' products come first and one check covers the tile: it compares raw
-  // logits with a per-row threshold, and the raise is a wave-uniform branch (the common tile pays
-  // max and compare instructions, no extra exponential).  One branch per tile instead of one per
-  // sub-tile leaves the scheduler one block of 64 products to interleave with the exponentials.
-  auto pass1_tile = [&](const u32x4 (&kt)[2][4], int tb, auto dirty_tag) {
-    f32x4 acc[2][NT];
-    sub_products(acc[0], kt[0]);
-    sub_products(acc[1], kt[1]);
-    if constexpr (decltype(dirty_tag)::value) {
-      sub_mask(acc[0], tb);
-      sub_mask(acc[1], tb + 16);
+  // Pass 2: every key's column sum of the rows' normalised weights; after the last row tile the 32 lanes
+  // of a half reduce their 16 keys' sums and each key's lanes store it.
+  float col[16];
+  auto pass2_sum = [&](const f32x16& acc, int t) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float w = __builtin_amdgcn_exp2f(fmaf(acc[i], p.scale_log2, -lse2[t]));
+      col[i] = t == 0 ? w : col[i] + w;
     }
-    float mx[NT];
-    bool raise = false;
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      mx[nt] = fmaxf(fmaxf(fmaxf(acc[0][nt][0], acc[0][nt][1]), fmaxf(acc[0][nt][2], acc[0][nt][3])),
-                     fmaxf(fmaxf(acc[1][nt][0], acc[1][nt][1]), fmaxf(acc[1][nt][2], acc[1][nt][3])));
-      raise |= mx[nt] > rthr[nt];
-    }
-    if (__builtin_expect(__builtin_amdgcn_ballot_w64(raise) != 0, 0)) {
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
-        if (mx[nt] > rthr[nt]) {
-          const float m2 = mx[nt] * p.scale_log2;    // scale > 0: the max commutes with it
-          rl[nt] = rl[nt] > 0.f ? rl[nt] * exp2f(rm[nt] - m2) : 0.f;
-          rm[nt] = m2;
-          rthr[nt] = (m2 + kSlack) / p.scale_log2;
-        }
-      }
-    }
-#pragma unroll
-    for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) rl[nt] += __builtin_amdgcn_exp2f(fmaf(acc[sub][nt][i], p.scale_log2, -rm[nt]));
   };
-
-  // Pass 2 over a 16-key sub-tile: each key's column sum of the rows' normalised weights.  After the
-  // 16-lane reduction every lane of a row holds the same four sums (each step adds a lane pair in
-  // both orders), so in a mask-free tile all 64 lanes store, four lanes per key with equal bits,
-  // and no branch splits the loop body: the next sub-tile's products can overlap this one's sums.
-  auto pass2_sub = [&](const u32x4 (&kr)[4], int tb, auto dirty_tag) {
-    constexpr bool dirty = decltype(dirty_tag)::value;
-    f32x4 acc[NT];
-    sub_products(acc, kr);
-    if constexpr (dirty) sub_mask(acc, tb);
-    float col[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) col[i] = __builtin_amdgcn_exp2f(fmaf(acc[0][i], p.scale_log2, -lse2[0]));
-#pragma unroll
-    for (int nt = 1; nt < NT; ++nt)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) col[i] += __builtin_amdgcn_exp2f(fmaf(acc[nt][i], p.scale_log2, -lse2[nt]));
-#pragma unroll
-    for (int i = 0; i < 4; ++i) col[i] = sum16(col[i]);
-    // opaque to the compiler, which would otherwise finish the reduction only for the column a lane
-    // stores, behind branches on the lane index
-    asm("" : "+v"(col[0]), "+v"(col[1]), "+v"(col[2]), "+v"(col[3]));
-    const int q = lr & 3;
-    const float v01 = (q & 1) ? col[1] : col[0], v23 = (q & 1) ? col[3] : col[2];
-    const float v = (q & 2) ? v23 : v01;
-    const int t = tb + q;
-    if constexpr (dirty) {
-      if (lr < 4 && t < k1) raw_part[t] = v;
-    } else {
-      raw_part[t] = v;                     // a mask-free tile lies inside the split: t < k1
-    }
+  const int my = half_sum_index(lane);
+  const int my_key = 8 * (my >> 2) + 4 * hf + (my & 3);
+  auto pass2_store = [&](int tb, bool checked) {
+    const float v = half_sums(col, lane);
+    const int key = tb + my_key;
+    if (!checked || key < k1) raw_part[key] = v;     // two lanes hold each key's sum, with equal bits
   };
 
   if (wave < ntiles) {
-    const uint32_t ring_lds = lds_addr(sm.ring[wave][0]);
-    const uint32_t roff_lds = lds_addr(sm.roff);
-    const uint32_t base16 = PAGED ? 0u : (uint32_t)(((int64_t)s * p.kv.stride_seq + (int64_t)g * p.kv.stride_head) >> 3);
-    const uint32_t tok16 = (uint32_t)(p.kv.stride_tok >> 3);
-    // pass 2 takes its tiles last first: pass 1 read them first to last, so the most recent (still in
-    // the memory-side cache) are read before the lines pass 1 read first are replaced
-    auto real = [&](int it) { return PASS == 2 ? ntiles - 1 - it : it; };
-    auto issue = [&](int tile, int slot) {
-      uint32_t r[2];
-      if constexpr (PAGED) {
-        if (tile >= ntiles) {
-          r[0] = r[1] = 0u;
-        } else if (page_arith) {
-          // sub-tile h (keys tb+16h .. +15) lies in one page: its offset + (key mod page_size) rows
-          const int tb = k0 + kTile * real(tile);
-          uint32_t a[2], w[2], b[2];
-#pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const int t = tb + 16 * h;
-            const int pi = div_small(t >> 4, psub, inv_psub);
-            a[h] = roff_lds + 4 * (uint32_t)(t < k1 ? pi - page0 : 0);   // past the split: entry 0, masked
-            w[h] = (uint32_t)(t - pi * p.kv.page_size);
-          }
-          asm volatile(
-              "ds_read_b32 %0, %2\n"
-              "ds_read_b32 %1, %3\n"
-              "s_waitcnt lgkmcnt(0)"
-              : "=&v"(b[0]), "=&v"(b[1])
-              : "v"(a[0]), "v"(a[1]));
-#pragma unroll
-          for (int h = 0; h < 2; ++h) r[h] = b[h] + (w[h] + (uint32_t)lr) * tok16;
-        } else {
-          read_krows(r, roff_lds, kTile * real(tile), lane);
-        }
-      } else if (tile >= ntiles) {
-        r[0] = r[1] = 0u;                  // padding: row 0, a safe, cache-resident address
-      } else {
-        const uint32_t r0 = base16 + (uint32_t)(k0 + kTile * real(tile)) * tok16;
-        r[0] = r0 + (uint32_t)lr * tok16;
-        r[1] = r0 + (uint32_t)(16 + lr) * tok16;
-      }
-      dma_ktile(p.kv.k, r, p.max_roff, sm.ring[wave][slot], lane);
-    };
-#pragma unroll
-    for (int q = 0; q < kRing; ++q) issue(wave + kWaves * q, q);
-    u32x4 kt[2][4];
+    if (PAGED) issue(wave, 0);
+    issue(wave + kWaves, 1);
     int j = 0;
-    // step j of this wave (tile wave + kWaves*j); true after its last tile
-    auto step = [&](auto dirty_tag) -> bool {
-      const int it = wave + kWaves * j, slot = j % kRing;
+    const int steps = (ntiles - wave + kWaves - 1) / kWaves;   // this wave's tiles: wave + kWaves*j, j < steps
+    const uint32_t koff = k_lane_off(lane);
+    // The tile of step j: its keys from LDS (read_tile), then its slot refilled (refill, once the keys
+    // have arrived in registers).  Returns the tile's first key.
+    auto read_tile = [&]() -> int {
       // the tile about to be read was issued (kRing-1) tiles before the newest
       static_assert(kRing == 2, "the wait below assumes one tile (8 loads) issued after the one read");
       asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-      read_ktile(kt, ring_lds + slot * kTileBytes, lane);
-      issue(it + kRing * kWaves, slot);
-      const int tb = k0 + kTile * real(it) + 4 * lg;
-      if constexpr (PASS == 1) {
-        pass1_tile(kt, tb, dirty_tag);
-      } else {
-        pass2_sub(kt[0], tb, dirty_tag);
-        pass2_sub(kt[1], tb + 16, dirty_tag);
+      const uint8_t* slot = sm.ring[wave][0] + (j % kRing) * kTileBytes;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) kt[c] = *reinterpret_cast<const bf16x8*>(slot + (koff ^ (16u * (uint32_t)c)));
+      return k0 + kTile * real(wave + kWaves * j);
+    };
+    auto refill = [&]() {
+      asm volatile("" : "+v"(kt[0]), "+v"(kt[1]), "+v"(kt[2]), "+v"(kt[3]), "+v"(kt[4]), "+v"(kt[5]), "+v"(kt[6]), "+v"(kt[7]) :: "memory");
+      issue(wave + kWaves * (j + kRing), j % kRing);
+    };
+    // Tiles that hold a masked key, one step after the other.
+    auto run_dirty = [&](int end) {
+      for (; j < end; ++j) {
+        const int tb = read_tile();
+        refill();
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+          f32x16 acc;
+          products(acc, t);
+          mask(acc, t, tb);
+          if constexpr (PASS == 1) pass1_sum(acc, t);
+          else pass2_sum(acc, t);
+        }
+        if constexpr (PASS == 2) pass2_store(tb, true);
       }
-      ++j;
-      return it + kWaves >= ntiles;
+    };
+    // Mask-free tiles, pipelined: the products of a row tile (or of the next tile's first) beside the
+    // exponentials and sums of the one before.
+    auto sum = [&](const f32x16& acc, int t) {
+      if constexpr (PASS == 1) pass1_sum(acc, t);
+      else pass2_sum(acc, t);
+    };
+    auto interleave = [] {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);       // one product
+        __builtin_amdgcn_sched_group_barrier(0x402, 6, 0);       // six vector instructions
+      }
+    };
+    auto run_clean = [&](int end) {
+      if (j >= end) return;
+      f32x16 acc[2];
+      int tb = read_tile();
+      products(acc[0], 0);
+      refill();
+      // tile of step j, its row tile 0's scores in acc[par]; true after the last
+      auto tile = [&](auto par_tag) -> bool {
+        constexpr int par = decltype(par_tag)::value;
+#pragma unroll
+        for (int t = 1; t < RT; ++t) {
+          products(acc[(par + t) & 1], t);
+          sum(acc[(par + t - 1) & 1], t - 1);
+          interleave();
+        }
+        const int tb0 = tb;
+        ++j;
+        if (j >= end) {
+          sum(acc[(par + RT - 1) & 1], RT - 1);
+          if constexpr (PASS == 2) pass2_store(tb0, false);
+          return true;
+        }
+        tb = read_tile();
+        products(acc[(par + RT) & 1], 0);
+        sum(acc[(par + RT - 1) & 1], RT - 1);
+        interleave();
+        if constexpr (PASS == 2) {
+          // the reduction after the sums: beside them its temporaries exceeded the registers
+          __builtin_amdgcn_sched_barrier(0);
+          pass2_store(tb0, false);
+        }
+        refill();
+        return false;
+      };
+      for (;;) {
+        if (tile(std::integral_constant<int, 0>{})) break;
+        if (RT % 2 == 1 && tile(std::integral_constant<int, 1>{})) break;
+      }
     };
     // a wave's tiles increase in pass 1, so its mask-free ones come first; in pass 2 they come last
-    bool last = false;
     if constexpr (PASS == 1) {
-      while (!last && wave + kWaves * j < first_dirty) last = step(std::integral_constant<bool, false>{});
-      while (!last) last = step(std::integral_constant<bool, true>{});
+      const int c = first_dirty - wave + kWaves - 1;             // c / kWaves steps lie below first_dirty
+      run_clean(c <= 0 ? 0 : (c / kWaves < steps ? c / kWaves : steps));
+      run_dirty(steps);
     } else {
-      while (!last && real(wave + kWaves * j) >= first_dirty) last = step(std::integral_constant<bool, true>{});
-      while (!last) last = step(std::integral_constant<bool, false>{});
+      const int c = ntiles - first_dirty - wave + kWaves - 1;    // c / kWaves steps lie at or past it
+      run_dirty(c <= 0 ? 0 : (c / kWaves < steps ? c / kWaves : steps));
+      run_clean(steps);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // padding loads land before the block ends
   }
 
   if constexpr (PASS == 1) {
-    // merge the 4 lane groups, then the waves, and publish per-row (max, sum) of this split
+    // merge the 2 lane halves, then the waves, and publish per-row (max, sum) of this split
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      if (!(rl[nt] > 0.f)) rm[nt] = -INFINITY;   // no visible key: the empty (max, sum)
-#pragma unroll
-      for (int m = 16; m <= 32; m <<= 1) {
-        const float m2 = shfl_xor_f(rm[nt], m), l2 = shfl_xor_f(rl[nt], m);
-        merge_ml(rm[nt], rl[nt], m2, l2);
-      }
-      if (lg == 0) {
-        sm.m[wave][16 * nt + lr] = rm[nt];
-        sm.l[wave][16 * nt + lr] = rl[nt];
+    for (int t = 0; t < RT; ++t) {
+      if (!(rl[t] > 0.f)) rm[t] = -INFINITY;   // no visible key: the empty (max, sum)
+      const float m2 = shfl_xor_f(rm[t], 32), l2 = shfl_xor_f(rl[t], 32);
+      merge_ml(rm[t], rl[t], m2, l2);
+      if (hf == 0) {
+        sm.m[wave][32 * t + lr] = rm[t];
+        sm.l[wave][32 * t + lr] = rl[t];
       }
     }
     __syncthreads();
-    if (tid < 16 * NT) {
+    if (tid < kRows) {
       float m = sm.m[0][tid], l = sm.l[0][tid];
       for (int w = 1; w < kWaves; ++w) merge_ml(m, l, sm.m[w][tid], sm.l[w][tid]);
       float* st = p.stats + stat_base + ((int64_t)split * kStatRows + tid) * 2;
@@ -553,7 +719,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(SelectParams p) {
   const int N = L - W, K = p.keep, rad = p.pool_kernel / 2;
   float* raw = p.raw ? p.raw + (int64_t)pair * p.max_L : nullptr;
   const float* part = p.raw_part + (int64_t)pair * p.n_rb * p.max_L;
-  constexpr int kStageBatch = 16;
+  constexpr int kStageBatch = 16, kStageRows = 2;
   for (int c0 = 0; c0 < L; c0 += kStageBatch * kTopkThreads) {
     float v[kStageBatch];
 #pragma unroll
@@ -561,12 +727,21 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(SelectParams p) {
       const int t = c0 + tid + e * kTopkThreads;
       v[e] = t < L ? part[t] : 0.f;
     }
-    for (int r = 1; r < p.n_rb; ++r) {
+    // the other row blocks, in order, kStageRows of them loaded at a time: one at a time, each cost a
+    // memory round trip (8 blocks of 16K scores: 49 us for the kernel, 23 us with two at a time; four gain nothing more)
+    for (int r0 = 1; r0 < p.n_rb; r0 += kStageRows) {
+      float y[kStageRows][kStageBatch];
 #pragma unroll
-      for (int e = 0; e < kStageBatch; ++e) {
-        const int t = c0 + tid + e * kTopkThreads;
-        if (t < L) v[e] += part[(int64_t)r * p.max_L + t];
-      }
+      for (int u = 0; u < kStageRows; ++u)
+#pragma unroll
+        for (int e = 0; e < kStageBatch; ++e) {
+          const int t = c0 + tid + e * kTopkThreads;
+          y[u][e] = r0 + u < p.n_rb && t < L ? part[(int64_t)(r0 + u) * p.max_L + t] : 0.f;
+        }
+#pragma unroll
+      for (int u = 0; u < kStageRows; ++u)
+#pragma unroll
+        for (int e = 0; e < kStageBatch; ++e) v[e] += y[u][e];
     }
 #pragma unroll
     for (int e = 0; e < kStageBatch; ++e) {
@@ -794,20 +969,22 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(SelectParams p) {
   }
 }
 
-template <int NT, bool PAGED>
+template <int RT, bool PAGED>
 hipError_t launch_scores(const SelectParams& p, int nblocks, hipStream_t stream) {
   if (!p.lse_win) {
-    hipLaunchKernelGGL((score_kernel<NT, PAGED, 1>), dim3(nblocks), dim3(kThreads), 0, stream, p);
+    hipLaunchKernelGGL((score_kernel<RT, PAGED, 1>), dim3(nblocks), dim3(kThreads), 0, stream, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((score_kernel<NT, PAGED, 2>), dim3(nblocks), dim3(kThreads), 0, stream, p);
+  hipLaunchKernelGGL((score_kernel<RT, PAGED, 2>), dim3(nblocks), dim3(kThreads), 0, stream, p);
   return hipGetLastError();
 }
 
-int select_nt(int R) {
-  const int tiles = (R + 15) / 16;
-  return tiles <= 1 ? 1 : tiles <= 2 ? 2 : tiles <= 4 ? 4 : 8;
+// 32-row tiles of a row block: n_rb blocks of at most 128 rows, of equal size
+int select_blocks(int R) { return (R + kStatRows - 1) / kStatRows; }
+int select_rt(int R) {
+  const int n_rb = select_blocks(R);
+  return ((R + n_rb - 1) / n_rb + 31) / 32;
 }
 
 }  // namespace
@@ -816,21 +993,34 @@ SelectPlan plan_select(int S, int Hkv, int Hq, int W, int max_L, bool paged, int
   SelectPlan pl;
   const int G = Hq / Hkv;
   const int R = W * G;
-  const int nt = select_nt(R);
-  pl.n_rb = (R + 16 * nt - 1) / (16 * nt);
+  pl.n_rb = select_blocks(R);
   const int64_t units = (int64_t)S * Hkv * pl.n_rb;
-  const int64_t per_block = (units * max_L + kTargetBlocks - 1) / kTargetBlocks;
   constexpr int64_t kStep = kWaves * kTile;
-  int64_t kps = (per_block + kStep - 1) / kStep * kStep;
-  const int64_t cap = ((int64_t)max_L + kStep - 1) / kStep * kStep;
-  if (kps > cap) kps = cap;
   // a paged split's table holds kSlotCap entries: one per key, or one per page when pages hold whole
   // 16-key sub-tiles (kps keys span at most kps / page_size + 2 pages); keys below 2^26 keep the
   // kernel's page division exact
   pl.page_arith = paged && page_size > 0 && page_size % 16 == 0 && max_L <= (1 << 26) - 64;
-  const int64_t paged_cap = pl.page_arith ? ((int64_t)(kSlotCap - 2) * page_size) / kStep * kStep : kMaxPagedKeys;
-  if (paged && kps > paged_cap) kps = paged_cap;
-  if (kps < kStep) kps = kStep;
+  const int64_t cap = !paged ? INT64_MAX
+                             : (pl.page_arith ? ((int64_t)(kSlotCap - 2) * page_size) / kStep * kStep : kMaxPagedKeys);
+  // Keys per split.  A CU holds one workgroup, so the launch runs in rounds of kTargetBlocks workgroups and
+  // the count that ends first is taken: rounds x (a split's keys + the fixed cost of a workgroup, ~7 us
+  // beside 2 us per 256 keys).  Just filling the CUs once, 18 sequences of 20K with 8 KV heads (144 units)
+  // took two splits each, 288 workgroups in two rounds, the second nearly empty; with five
+  // each (2.8 rounds of a fifth) the two passes take 129 + 141 us there instead of 226 + 210 (the row
+  // tiles of this kernel included).
+  // Only the largest split counts of 1, 2, ... whole rounds can be best.
+  constexpr int64_t kFixedKeys = 768;
+  const int64_t whole = max_L > 0 ? (max_L + kStep - 1) / kStep * kStep : kStep;
+  int64_t kps = whole, best = INT64_MAX;
+  for (int64_t r = 1; r <= 16; ++r) {
+    int64_t ns = kTargetBlocks * r / units;
+    if (ns < 1) ns = 1;
+    int64_t k = (whole / kStep + ns - 1) / ns * kStep;
+    if (k > cap) k = cap;
+    const int64_t blocks = units * ((whole + k - 1) / k);
+    const int64_t cost = (blocks + kTargetBlocks - 1) / kTargetBlocks * (k + kFixedKeys);
+    if (cost < best) { best = cost; kps = k; }
+  }
   pl.kps = (int)kps;
   pl.nsplit = max_L > 0 ? (int)((max_L + kps - 1) / kps) : 1;
   pl.stats_bytes = align256(sizeof(float) * (size_t)units * pl.nsplit * kStatRows * 2);
@@ -840,14 +1030,13 @@ SelectPlan plan_select(int S, int Hkv, int Hq, int W, int max_L, bool paged, int
 }
 
 hipError_t launch_select(const SelectParams& p, bool paged, hipStream_t stream) {
-  const int nt = select_nt(p.R);
   const int nblocks = p.S * p.Hkv * p.n_rb * p.nsplit;
   hipError_t e = hipSuccess;
-  switch (nt) {
+  switch (select_rt(p.R)) {
     case 1: e = paged ? launch_scores<1, true>(p, nblocks, stream) : launch_scores<1, false>(p, nblocks, stream); break;
     case 2: e = paged ? launch_scores<2, true>(p, nblocks, stream) : launch_scores<2, false>(p, nblocks, stream); break;
-    case 4: e = paged ? launch_scores<4, true>(p, nblocks, stream) : launch_scores<4, false>(p, nblocks, stream); break;
-    default: e = paged ? launch_scores<8, true>(p, nblocks, stream) : launch_scores<8, false>(p, nblocks, stream); break;
+    case 3: e = paged ? launch_scores<3, true>(p, nblocks, stream) : launch_scores<3, false>(p, nblocks, stream); break;
+    default: e = paged ? launch_scores<4, true>(p, nblocks, stream) : launch_scores<4, false>(p, nblocks, stream); break;
   }
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(topk_kernel, dim3(p.S * p.Hkv), dim3(kTopkThreads), 0, stream, p);

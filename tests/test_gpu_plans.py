@@ -6,7 +6,11 @@ the operation's own tests.
 """
 import numpy as np
 import pytest
+import torch
 
+import paper_2606_00144_amd as bd
+import synth
+from gpu_utils import bf16_dev, case, check_selection, i32_dev, oracle_scores, paged_kv
 from mv_check import _rand_bits, _run
 
 pytestmark = pytest.mark.gpu
@@ -27,3 +31,57 @@ def test_block_workgroup_rounds(S, Hkv, G, C, L, ld, seqs):
         for h in range(Hkv):
             idx_v[0, s, h] = np.sort(g.choice(lens[s], ld, replace=False))
     _run(k, v, qb, idx_v, np.full((1, S), ld, np.int32), lens, f"rounds S={S}", seqs=seqs, seed=7)
+
+
+def _select_inputs(lens, Hkv, W, G, seed):
+    """Keys whose norm grows with the position, so that a row's reference is raised again and again."""
+    g = np.random.default_rng(seed)
+    q = synth.f32_to_bf16_bits(g.standard_normal((len(lens), W, Hkv * G, 128)).astype(np.float32))
+    ks = [synth.f32_to_bf16_bits((g.standard_normal((Hkv, n, 128)) * (0.2 + 5.0 * np.arange(n)[None, :, None] / n)
+                                  ).astype(np.float32)) for n in lens]
+    return q, ks
+
+
+def _select_case(q, ks, lens, Hkv, W, G, B, layout):
+    Hq, L = Hkv * G, max(lens)
+    table = None
+    if layout.startswith("page"):
+        P = int(layout[4:])
+        npg = [(n + P - 1) // P for n in lens]
+        perm = np.random.default_rng(5).permutation(sum(npg) + 3)
+        t, at = np.full((len(lens), max(npg)), -1, np.int32), 0
+        for s, n in enumerate(npg):
+            t[s, :n] = perm[at:at + n]
+            at += n
+        kd, _ = paged_kv(ks, ks, t, sum(npg) + 3, P)
+        table = i32_dev(t)
+    else:
+        k = np.zeros((len(lens), Hkv, L, 128), np.uint16)
+        for s, n in enumerate(lens):
+            k[s, :, :n] = ks[s]
+        kd = bf16_dev(k)
+        if layout == "token-major":             # rows of one head Hkv * 128 elements apart
+            kd = kd.transpose(1, 2).contiguous().transpose(1, 2)
+    case(f"select rows={W * G} {layout} S={len(lens)}")
+    idx, nsel, sc = bd.bd_select_kv(kd, bf16_dev(q), i32_dev(lens), B, return_scores=True, page_table=table, max_seq_len=L)
+    torch.cuda.synchronize()
+    raws = oracle_scores(ks, q, lens, Hq)
+    check_selection(idx.cpu().numpy(), nsel.cpu().numpy(), sc.cpu().numpy(), raws, lens, W, B,
+                    f"rows {W * G} {layout}", Hq=Hq)
+
+
+@pytest.mark.parametrize("layout", ["contiguous", "token-major", "page16", "page24", "page64"])
+@pytest.mark.parametrize("W,G", [(1, 1), (33, 1), (13, 5), (31, 4), (35, 5), (86, 3)])
+def test_select_row_tiles(W, G, layout):
+    # 1..4 row tiles of 32, one and several row blocks, a remainder in each; splits and tiles cut short
+    lens = [1033, 700, 289]
+    q, ks = _select_inputs(lens, 2, W, G, 41)
+    _select_case(q, ks, lens, 2, W, G, 128, layout)
+
+
+@pytest.mark.parametrize("S,Hkv", [(36, 4), (65, 4), (3, 2)])
+def test_select_split_rounds(S, Hkv):
+    # 144 units (several splits each, whole rounds), 260 (one more than a round), 6 (every key block a split)
+    lens = [520 + 7 * (s % 5) for s in range(S)]
+    q, ks = _select_inputs(lens, Hkv, 8, 4, 43)
+    _select_case(q, ks, lens, Hkv, 8, 4, 96, "contiguous")
