@@ -19,8 +19,10 @@ KV caches are bf16 tensors, either contiguous ``[S][Hkv][L][128]`` or paged
 from __future__ import annotations
 
 import ctypes
+import functools
 import math
 import os
+import struct
 import threading
 from typing import Optional
 
@@ -59,7 +61,10 @@ class KvDesc(ctypes.Structure):
 
 _P = ctypes.c_void_p
 _I32, _I64, _F32, _SZ = ctypes.c_int32, ctypes.c_int64, ctypes.c_float, ctypes.c_size_t
-_KV = ctypes.POINTER(KvDesc)
+_KV = ctypes.c_void_p        # a KvDesc (byref, pointer) or its bytes
+_KV_BYTES = struct.Struct("@PPiiiiPqqqPiiiq")
+assert _KV_BYTES.size == ctypes.sizeof(KvDesc)
+_BF16, _I32T, _F32T = torch.bfloat16, torch.int32, torch.float32
 
 _SIGNATURES = {
     "bd_status_string": (ctypes.c_char_p, [_I32]),
@@ -93,6 +98,10 @@ _lib_lock = threading.Lock()
 
 def lib() -> ctypes.CDLL:
     """The loaded libbd.so with argument types set.  Raises if it is not built."""
+    return _lib if _lib is not None else _load()
+
+
+def _load() -> ctypes.CDLL:
     global _lib
     with _lib_lock:
         if _lib is None:
@@ -107,6 +116,12 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
+@functools.lru_cache(maxsize=1024)
+def _ws_bytes(entry: str, *shape: int) -> int:
+    """Scratch bytes of `entry` for these sizes: a function of the sizes alone."""
+    return getattr(lib(), entry)(*shape)
+
+
 def _check(status: int) -> None:
     if status != BD_OK:
         raise BdError(status, lib().bd_last_error().decode())
@@ -116,12 +131,23 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# The current stream of the current device as the handle alone: building torch's Stream object for it costs
+# more than the rest of a call's marshalling of one tensor.
+_get_device = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_get_device())
+
+
+_DEFAULT_SCALE = 1.0 / math.sqrt(HEAD_DIM)
 
 
 def _scale(scale: Optional[float]) -> float:
-    return 1.0 / math.sqrt(HEAD_DIM) if scale is None else float(scale)
+    return _DEFAULT_SCALE if scale is None else float(scale)
 
 
 def _require(cond: bool, msg: str) -> None:
@@ -129,36 +155,45 @@ def _require(cond: bool, msg: str) -> None:
         raise BdError(BD_ERR_INVALID_ARG, msg)
 
 
+def _kv(k, v, seq_lens, page_table=None, max_seq_len=None):
+    """The bytes of a KvDesc for these tensors (checked), and its (num_seqs, num_kv_heads, max_seq_len)."""
+    ks, st = k.shape, k.stride()
+    if not (k.dtype == _BF16 and len(ks) == 4 and ks[3] == HEAD_DIM and st[3] == 1):
+        raise BdError(BD_ERR_INVALID_ARG, "k must be bf16 [*, Hkv, *, 128] with a contiguous last dimension")
+    vp = 0
+    if v is not None:
+        if not (v.dtype == _BF16 and v.shape == ks and v.stride() == st):
+            raise BdError(BD_ERR_INVALID_ARG, "v must match k in shape and strides")
+        vp = v.data_ptr()
+    ls = seq_lens.shape
+    if not (seq_lens.dtype == _I32T and len(ls) == 1):
+        raise BdError(BD_ERR_INVALID_ARG, "seq_lens must be int32 [S]")
+    S, (n0, hkv, n2, _) = ls[0], ks
+    if page_table is None:
+        if n0 != S:
+            raise BdError(BD_ERR_INVALID_ARG, "contiguous k must be [S, Hkv, L, 128]")
+        L = n2 if max_seq_len is None else int(max_seq_len)
+        return _pack_kv(k.data_ptr(), vp, S, hkv, HEAD_DIM, L, seq_lens.data_ptr(), st[0], st[1], st[2],
+                        0, 0, 0, 0, 0), S, hkv, L
+    ps = page_table.shape
+    if not (page_table.dtype == _I32T and len(ps) == 2 and ps[0] == S):
+        raise BdError(BD_ERR_INVALID_ARG, "page_table must be int32 [S, max_pages]")
+    L = ps[1] * n2 if max_seq_len is None else int(max_seq_len)
+    return _pack_kv(k.data_ptr(), vp, S, hkv, HEAD_DIM, L, seq_lens.data_ptr(), 0, st[1], st[2],
+                    page_table.data_ptr(), n2, ps[1], n0, st[0]), S, hkv, L
+
+
+def _pack_kv(*fields) -> bytes:
+    try:
+        return _KV_BYTES.pack(*fields)
+    except struct.error:                 # a size beyond its field: ctypes keeps the low bits, the library checks them
+        return bytes(KvDesc(*fields))
+
+
 def kv_desc(k: torch.Tensor, v: Optional[torch.Tensor], seq_lens: torch.Tensor,
             page_table: Optional[torch.Tensor] = None, max_seq_len: Optional[int] = None) -> KvDesc:
     """Describe a KV cache for the C ABI (tensors must outlive the call)."""
-    _require(k.dtype == torch.bfloat16 and k.dim() == 4 and k.shape[3] == HEAD_DIM and k.stride(3) == 1,
-             "k must be bf16 [*, Hkv, *, 128] with a contiguous last dimension")
-    if v is not None:
-        _require(v.dtype == torch.bfloat16 and v.shape == k.shape and v.stride() == k.stride(),
-                 "v must match k in shape and strides")
-    _require(seq_lens.dtype == torch.int32 and seq_lens.dim() == 1, "seq_lens must be int32 [S]")
-    d = KvDesc()
-    d.k, d.v = k.data_ptr(), (v.data_ptr() if v is not None else None)
-    d.num_seqs = seq_lens.shape[0]
-    d.num_kv_heads = k.shape[1]
-    d.head_dim = k.shape[3]
-    d.seq_lens = seq_lens.data_ptr()
-    d.stride_head, d.stride_tok = k.stride(1), k.stride(2)
-    if page_table is None:
-        _require(k.shape[0] == seq_lens.shape[0], "contiguous k must be [S, Hkv, L, 128]")
-        d.max_seq_len = k.shape[2] if max_seq_len is None else int(max_seq_len)
-        d.stride_seq = k.stride(0)
-    else:
-        _require(page_table.dtype == torch.int32 and page_table.dim() == 2 and page_table.shape[0] == seq_lens.shape[0],
-                 "page_table must be int32 [S, max_pages]")
-        d.page_table = page_table.data_ptr()
-        d.page_size = k.shape[2]
-        d.max_pages_per_seq = page_table.shape[1]
-        d.num_pages = k.shape[0]
-        d.stride_page = k.stride(0)
-        d.max_seq_len = page_table.shape[1] * k.shape[2] if max_seq_len is None else int(max_seq_len)
-    return d
+    return KvDesc.from_buffer_copy(_kv(k, v, seq_lens, page_table, max_seq_len)[0])
 
 
 class Workspace:
@@ -175,21 +210,27 @@ class Workspace:
     def get(self, nbytes: int, device) -> Optional[torch.Tensor]:
         if nbytes == 0:
             return None
-        if self.buf is None or self.buf.numel() < nbytes + 256 or self.buf.device != torch.device(device):
-            self.buf = torch.zeros(nbytes + 256, dtype=torch.uint8, device=device)
-        return self.buf
+        buf = self.buf
+        if buf is None or buf.numel() < nbytes + 256 or buf.device != torch.device(device):
+            buf = self.buf = torch.zeros(nbytes + 256, dtype=torch.uint8, device=device)
+        return buf
 
 
 _default_ws = {}
 
 
-def _ws(op: str, nbytes: int, device, workspace: Optional[Workspace]):
+def _ws(op: str, nbytes: int, like: torch.Tensor, stream: int, workspace: Optional[Workspace]):
+    """Address and size of `nbytes` of scratch on `like`'s device, 256-byte aligned."""
     if workspace is None:
-        key = (op, torch.device(device).index, _stream())
-        workspace = _default_ws.setdefault(key, Workspace())
-    buf = workspace.get(nbytes, device)
-    if buf is None:
+        key = (op, like.get_device(), stream)
+        workspace = _default_ws.get(key)
+        if workspace is None:
+            workspace = _default_ws.setdefault(key, Workspace())
+    if nbytes == 0:
         return None, 0
+    buf = workspace.buf
+    if buf is None or buf.numel() < nbytes + 256 or buf.device != like.device:
+        buf = workspace.get(nbytes, like.device)
     base = buf.data_ptr()
     aligned = (base + 255) & ~255
     return aligned, buf.numel() - (aligned - base)
@@ -221,37 +262,41 @@ def bd_select_kv_chunks(k: torch.Tensor, q_win: torch.Tensor, seq_lens: torch.Te
                    scale, lse_win, return_scores, page_table, max_seq_len, workspace, outputs)
 
 
-def _out(given, shape, dtype, dev, what):
-    """A caller-given output (checked) or a new one."""
+def _out(given, shape, dtype, like, what):
+    """A caller-given output (checked) or a new one on `like`'s device."""
     if given is None:
-        return torch.empty(shape, dtype=dtype, device=dev)
+        return like.new_empty(shape, dtype=dtype)
     _require(given.dtype == dtype and tuple(given.shape) == tuple(shape) and given.is_contiguous(),
              f"{what} must be contiguous {dtype} {tuple(shape)}")
     return given
 
 
+def _out_like(given, q, what):
+    """A caller-given output shaped like the contiguous tensor q (checked) or a new one."""
+    if given is None:
+        return torch.empty_like(q, memory_format=torch.contiguous_format)
+    return _out(given, q.shape, q.dtype, q, what)
+
+
 def _select(entry, mode_args, ld, k, q_win, seq_lens, budget, scale, lse_win, return_scores, page_table, max_seq_len,
             workspace, outputs=None):
     _require(q_win.dtype == torch.bfloat16 and q_win.dim() == 4 and q_win.is_contiguous(), "q_win must be contiguous bf16 [S,W,Hq,128]")
-    kv = kv_desc(k, None, seq_lens, page_table, max_seq_len)
-    S, W, Hq = q_win.shape[0], q_win.shape[1], q_win.shape[2]
-    dev = q_win.device
+    kv, _, hkv, L = _kv(k, None, seq_lens, page_table, max_seq_len)
+    S, W, Hq, _ = q_win.shape
     given = tuple(outputs) + (None,) * 3 if outputs is not None else (None,) * 3
-    idx = _out(given[0], (S, kv.num_kv_heads, ld), torch.int32, dev, "idx")
-    nsel = _out(given[1], (S,), torch.int32, dev, "nsel")
+    idx = _out(given[0], (S, hkv, ld), torch.int32, q_win, "idx")
+    nsel = _out(given[1], (S,), torch.int32, q_win, "nsel")
     scores = None
     if return_scores:
-        scores = given[2] if given[2] is not None else torch.zeros((S, kv.num_kv_heads, kv.max_seq_len),
-                                                                    dtype=torch.float32, device=dev)
-        _require(scores.dtype == torch.float32 and tuple(scores.shape) == (S, kv.num_kv_heads, kv.max_seq_len)
+        scores = given[2] if given[2] is not None else torch.zeros((S, hkv, L), dtype=torch.float32, device=q_win.device)
+        _require(scores.dtype == torch.float32 and tuple(scores.shape) == (S, hkv, L)
                  and scores.is_contiguous(), "scores must be contiguous fp32 [S,Hkv,max_seq_len]")
     if lse_win is not None:
         _require(lse_win.dtype == torch.float32 and lse_win.is_contiguous() and lse_win.shape == (S, W, Hq), "lse_win must be fp32 [S,W,Hq]")
-    L = lib()
-    nb = L.bd_select_kv_workspace_bytes(S, kv.num_kv_heads, Hq, W, kv.max_seq_len)
-    wp, wb = _ws("select", nb, dev, workspace)
-    _check(getattr(L, entry)(ctypes.byref(kv), q_win.data_ptr(), Hq, W, budget, *mode_args, _scale(scale),
-                             _ptr(lse_win), idx.data_ptr(), nsel.data_ptr(), _ptr(scores), wp, wb, _stream()))
+    stream = _stream()
+    wp, wb = _ws("select", _ws_bytes("bd_select_kv_workspace_bytes", S, hkv, Hq, W, L), q_win, stream, workspace)
+    _check(getattr(lib(), entry)(kv, q_win.data_ptr(), Hq, W, budget, *mode_args, _scale(scale),
+                                 _ptr(lse_win), idx.data_ptr(), nsel.data_ptr(), _ptr(scores), wp, wb, stream))
     return (idx, nsel, scores) if return_scores else (idx, nsel)
 
 
@@ -262,18 +307,22 @@ def bd_sparse_decode_attn(k: torch.Tensor, v: torch.Tensor, q: torch.Tensor, idx
                           workspace: Optional[Workspace] = None):
     """Drafter decode attention over selected entries.  q: bf16 [S, Hq, 128]; idx int32 [S, Hkv, ld].
     out / lse: optional preallocated outputs."""
-    _require(q.dtype == torch.bfloat16 and q.dim() == 3 and q.is_contiguous(), "q must be contiguous bf16 [S,Hq,128]")
-    _require(idx.dtype == torch.int32 and idx.dim() == 3 and idx.is_contiguous(), "idx must be contiguous int32 [S,Hkv,ld]")
-    _require(nsel.dtype == torch.int32 and nsel.is_contiguous(), "nsel must be int32 [S]")
-    kv = kv_desc(k, v, seq_lens, page_table, max_seq_len)
-    S, Hq = q.shape[0], q.shape[1]
-    out = _out(out, q.shape, torch.bfloat16, q.device, "out")
-    lse = _out(lse, (S, Hq), torch.float32, q.device, "lse") if return_lse else None
-    L = lib()
-    nb = L.bd_sparse_decode_attn_workspace_bytes(S, kv.num_kv_heads, Hq, idx.shape[2])
-    wp, wb = _ws("decode", nb, q.device, workspace)
-    _check(L.bd_sparse_decode_attn(ctypes.byref(kv), q.data_ptr(), Hq, idx.data_ptr(), idx.shape[2], nsel.data_ptr(),
-                                   _scale(scale), out.data_ptr(), _ptr(lse), wp, wb, _stream()))
+    qs, xs = q.shape, idx.shape
+    if not (q.dtype == _BF16 and len(qs) == 3 and q.is_contiguous()):
+        raise BdError(BD_ERR_INVALID_ARG, "q must be contiguous bf16 [S,Hq,128]")
+    if not (idx.dtype == _I32T and len(xs) == 3 and idx.is_contiguous()):
+        raise BdError(BD_ERR_INVALID_ARG, "idx must be contiguous int32 [S,Hkv,ld]")
+    if not (nsel.dtype == _I32T and nsel.is_contiguous()):
+        raise BdError(BD_ERR_INVALID_ARG, "nsel must be int32 [S]")
+    kv, _, hkv, _ = _kv(k, v, seq_lens, page_table, max_seq_len)
+    S, Hq, _ = qs
+    ld = xs[2]
+    out = _out_like(out, q, "out")
+    lse = _out(lse, (S, Hq), _F32T, q, "lse") if return_lse else None
+    stream = _stream()
+    wp, wb = _ws("decode", _ws_bytes("bd_sparse_decode_attn_workspace_bytes", S, hkv, Hq, ld), q, stream, workspace)
+    _check(lib().bd_sparse_decode_attn(kv, q.data_ptr(), Hq, idx.data_ptr(), ld, nsel.data_ptr(), _scale(scale),
+                                       out.data_ptr(), _ptr(lse), wp, wb, stream))
     return (out, lse) if return_lse else out
 
 
@@ -288,27 +337,26 @@ def bd_multiview_attn(k: torch.Tensor, v: torch.Tensor, q_blk: torch.Tensor, idx
     preallocated tensors in that order (None entries are allocated).
     """
     _require(q_blk.dtype == torch.bfloat16 and q_blk.dim() == 4 and q_blk.is_contiguous(), "q_blk must be contiguous bf16 [S,C,Hq,128]")
-    kv = kv_desc(k, v, seq_lens, page_table, max_seq_len)
-    S, C, Hq = q_blk.shape[0], q_blk.shape[1], q_blk.shape[2]
+    kv, _, hkv, L = _kv(k, v, seq_lens, page_table, max_seq_len)
+    S, C, Hq, _ = q_blk.shape
     V = 0 if idx_views is None else idx_views.shape[0]
     ld = 0 if idx_views is None else idx_views.shape[3]
     if V:
         _require(idx_views.dtype == torch.int32 and idx_views.is_contiguous(), "idx_views must be contiguous int32 [V,S,Hkv,ld]")
         _require(nsel_views is not None and nsel_views.dtype == torch.int32 and nsel_views.shape == (V, S), "nsel_views must be int32 [V,S]")
-    dev = q_blk.device
     given = tuple(outputs) + (None,) * 6 if outputs is not None else (None,) * 6
-    out_v = _out(given[0], (V, S, C, Hq, HEAD_DIM), torch.bfloat16, dev, "out_views") if V else None
-    out_f = _out(given[1], (S, C, Hq, HEAD_DIM), torch.bfloat16, dev, "out_full") if full else None
-    o32_v = _out(given[2], (V, S, C, Hq, HEAD_DIM), torch.float32, dev, "out32_views") if (V and train) else None
-    lse_v = _out(given[3], (V, S, C, Hq), torch.float32, dev, "lse_views") if (V and train) else None
-    o32_f = _out(given[4], (S, C, Hq, HEAD_DIM), torch.float32, dev, "out32_full") if (full and train) else None
-    lse_f = _out(given[5], (S, C, Hq), torch.float32, dev, "lse_full") if (full and train) else None
-    L = lib()
-    nb = L.bd_multiview_attn_workspace_bytes(S, kv.num_kv_heads, Hq, C, V, ld, kv.max_seq_len, int(full))
-    wp, wb = _ws("multiview", nb, dev, workspace)
-    _check(L.bd_multiview_attn(ctypes.byref(kv), q_blk.data_ptr(), Hq, C, V, _ptr(idx_views), ld, _ptr(nsel_views),
-                               _scale(scale), _ptr(out_v), _ptr(lse_v), _ptr(o32_v), _ptr(out_f), _ptr(lse_f),
-                               _ptr(o32_f), wp, wb, _stream()))
+    out_v = _out(given[0], (V, S, C, Hq, HEAD_DIM), torch.bfloat16, q_blk, "out_views") if V else None
+    out_f = _out(given[1], (S, C, Hq, HEAD_DIM), torch.bfloat16, q_blk, "out_full") if full else None
+    o32_v = _out(given[2], (V, S, C, Hq, HEAD_DIM), torch.float32, q_blk, "out32_views") if (V and train) else None
+    lse_v = _out(given[3], (V, S, C, Hq), torch.float32, q_blk, "lse_views") if (V and train) else None
+    o32_f = _out(given[4], (S, C, Hq, HEAD_DIM), torch.float32, q_blk, "out32_full") if (full and train) else None
+    lse_f = _out(given[5], (S, C, Hq), torch.float32, q_blk, "lse_full") if (full and train) else None
+    stream = _stream()
+    nb = _ws_bytes("bd_multiview_attn_workspace_bytes", S, hkv, Hq, C, V, ld, L, int(full))
+    wp, wb = _ws("multiview", nb, q_blk, stream, workspace)
+    _check(lib().bd_multiview_attn(kv, q_blk.data_ptr(), Hq, C, V, _ptr(idx_views), ld, _ptr(nsel_views),
+                                   _scale(scale), _ptr(out_v), _ptr(lse_v), _ptr(o32_v), _ptr(out_f), _ptr(lse_f),
+                                   _ptr(o32_f), wp, wb, stream))
     return (out_v, out_f, o32_v, lse_v, o32_f, lse_f) if train else (out_v, out_f)
 
 
@@ -324,8 +372,8 @@ def bd_multiview_attn_bwd(k: torch.Tensor, v: torch.Tensor, q_blk: torch.Tensor,
     the upstream gradients (bf16, shaped like the outputs).  Returns (dq [S,C,Hq,128], dk_blk, dv_blk [S,C,Hkv,128]) in fp32;
     dk_blk and dv_blk are None unless with_dkv."""
     _require(q_blk.dtype == torch.bfloat16 and q_blk.dim() == 4 and q_blk.is_contiguous(), "q_blk must be contiguous bf16 [S,C,Hq,128]")
-    kv = kv_desc(k, v, seq_lens, page_table, max_seq_len)
-    S, C, Hq = q_blk.shape[0], q_blk.shape[1], q_blk.shape[2]
+    kv, _, hkv, L = _kv(k, v, seq_lens, page_table, max_seq_len)
+    S, C, Hq, _ = q_blk.shape
     V = 0 if idx_views is None else idx_views.shape[0]
     ld = 0 if idx_views is None else idx_views.shape[3]
     if V:
@@ -341,18 +389,17 @@ def bd_multiview_attn_bwd(k: torch.Tensor, v: torch.Tensor, q_blk: torch.Tensor,
                            (lse_full, (S, C, Hq), torch.float32)):
             _require(t is not None and t.dtype == dt and tuple(t.shape) == shp and t.is_contiguous(),
                      f"full-branch tensors must be contiguous {dt} {shp}")
-    dev = q_blk.device
     given = tuple(grads) + (None,) * 3 if grads is not None else (None,) * 3
-    dq = _out(given[0], (S, C, Hq, HEAD_DIM), torch.float32, dev, "dq")
-    dk = _out(given[1], (S, C, kv.num_kv_heads, HEAD_DIM), torch.float32, dev, "dk") if with_dkv else None
-    dv = _out(given[2], (S, C, kv.num_kv_heads, HEAD_DIM), torch.float32, dev, "dv") if with_dkv else None
-    L = lib()
-    nb = L.bd_multiview_attn_bwd_workspace_bytes(S, kv.num_kv_heads, Hq, C, V, ld, kv.max_seq_len, int(full))
-    wp, wb = _ws("multiview_bwd", nb, dev, workspace)
-    _check(L.bd_multiview_attn_bwd(ctypes.byref(kv), q_blk.data_ptr(), Hq, C, V, _ptr(idx_views), ld,
-                                   _ptr(nsel_views), _scale(scale), _ptr(out32_views), _ptr(lse_views),
-                                   _ptr(dout_views), _ptr(out32_full), _ptr(lse_full), _ptr(dout_full),
-                                   dq.data_ptr(), _ptr(dk), _ptr(dv), wp, wb, _stream()))
+    dq = _out(given[0], (S, C, Hq, HEAD_DIM), torch.float32, q_blk, "dq")
+    dk = _out(given[1], (S, C, hkv, HEAD_DIM), torch.float32, q_blk, "dk") if with_dkv else None
+    dv = _out(given[2], (S, C, hkv, HEAD_DIM), torch.float32, q_blk, "dv") if with_dkv else None
+    stream = _stream()
+    nb = _ws_bytes("bd_multiview_attn_bwd_workspace_bytes", S, hkv, Hq, C, V, ld, L, int(full))
+    wp, wb = _ws("multiview_bwd", nb, q_blk, stream, workspace)
+    _check(lib().bd_multiview_attn_bwd(kv, q_blk.data_ptr(), Hq, C, V, _ptr(idx_views), ld,
+                                       _ptr(nsel_views), _scale(scale), _ptr(out32_views), _ptr(lse_views),
+                                       _ptr(dout_views), _ptr(out32_full), _ptr(lse_full), _ptr(dout_full),
+                                       dq.data_ptr(), _ptr(dk), _ptr(dv), wp, wb, stream))
     return dq, dk, dv
 
 
@@ -362,17 +409,17 @@ def bd_verify_attn(k: torch.Tensor, v: torch.Tensor, q: torch.Tensor, seq_lens: 
                    lse: Optional[torch.Tensor] = None, workspace: Optional[Workspace] = None):
     """Verifier attention at the gamma+1 draft positions.  q: bf16 [S, gamma+1, Hq, 128].
     out / lse: optional preallocated outputs."""
-    _require(q.dtype == torch.bfloat16 and q.dim() == 4 and q.is_contiguous(), "q must be contiguous bf16 [S,gamma+1,Hq,128]")
-    kv = kv_desc(k, v, seq_lens, page_table, max_seq_len)
-    S, R, Hq = q.shape[0], q.shape[1], q.shape[2]
+    qs = q.shape
+    if not (q.dtype == _BF16 and len(qs) == 4 and q.is_contiguous()):
+        raise BdError(BD_ERR_INVALID_ARG, "q must be contiguous bf16 [S,gamma+1,Hq,128]")
+    kv, _, hkv, L = _kv(k, v, seq_lens, page_table, max_seq_len)
+    S, R, Hq, _ = qs
     gamma = R - 1
-    out = _out(out, q.shape, torch.bfloat16, q.device, "out")
-    lse = _out(lse, (S, R, Hq), torch.float32, q.device, "lse") if return_lse else None
-    L = lib()
-    nb = L.bd_verify_attn_workspace_bytes(S, kv.num_kv_heads, Hq, gamma, kv.max_seq_len)
-    wp, wb = _ws("verify", nb, q.device, workspace)
-    _check(L.bd_verify_attn(ctypes.byref(kv), q.data_ptr(), Hq, gamma, _scale(scale), out.data_ptr(), _ptr(lse),
-                            wp, wb, _stream()))
+    out = _out_like(out, q, "out")
+    lse = _out(lse, (S, R, Hq), _F32T, q, "lse") if return_lse else None
+    stream = _stream()
+    wp, wb = _ws("verify", _ws_bytes("bd_verify_attn_workspace_bytes", S, hkv, Hq, gamma, L), q, stream, workspace)
+    _check(lib().bd_verify_attn(kv, q.data_ptr(), Hq, gamma, _scale(scale), out.data_ptr(), _ptr(lse), wp, wb, stream))
     return (out, lse) if return_lse else out
 
 
@@ -385,8 +432,8 @@ def bd_verify_attn_noalloc(k: torch.Tensor, v: torch.Tensor, q: torch.Tensor, se
     _require(out.dtype == torch.bfloat16 and out.shape == q.shape and out.is_contiguous(), "out must be shaped like q")
     if lse is not None:
         _require(lse.dtype == torch.float32 and lse.shape == q.shape[:3] and lse.is_contiguous(), "lse must be fp32 [S,gamma+1,Hq]")
-    kv = kv_desc(k, v, seq_lens, page_table, max_seq_len)
-    _check(lib().bd_verify_attn_noalloc(ctypes.byref(kv), q.data_ptr(), q.shape[2], q.shape[1] - 1, _scale(scale),
+    kv = _kv(k, v, seq_lens, page_table, max_seq_len)[0]
+    _check(lib().bd_verify_attn_noalloc(kv, q.data_ptr(), q.shape[2], q.shape[1] - 1, _scale(scale),
                                         out.data_ptr(), _ptr(lse), _stream()))
 
 
@@ -406,11 +453,10 @@ def bd_accept_len(logits: torch.Tensor, draft: torch.Tensor, *, return_argmax: b
         am = torch.empty((S, R), dtype=torch.int32, device=dev) if return_argmax else None
     else:
         acc, bonus, am = outputs
-    L = lib()
-    nb = L.bd_accept_len_workspace_bytes(S, gamma, V)
-    wp, wb = _ws("accept", nb, dev, workspace)
-    _check(L.bd_accept_len(logits.data_ptr(), logits.stride(1), draft.data_ptr(), S, gamma, V, acc.data_ptr(),
-                           bonus.data_ptr(), _ptr(am), wp, wb, _stream()))
+    stream = _stream()
+    wp, wb = _ws("accept", _ws_bytes("bd_accept_len_workspace_bytes", S, gamma, V), logits, stream, workspace)
+    _check(lib().bd_accept_len(logits.data_ptr(), logits.stride(1), draft.data_ptr(), S, gamma, V, acc.data_ptr(),
+                               bonus.data_ptr(), _ptr(am), wp, wb, stream))
     return (acc, bonus, am) if return_argmax else (acc, bonus)
 
 
@@ -425,9 +471,9 @@ def bd_cache_append(k: torch.Tensor, v: torch.Tensor, seq_lens: torch.Tensor, k_
     if idx is not None:
         _require(idx.dtype == torch.int32 and idx.dim() == 3 and idx.is_contiguous(), "idx must be contiguous int32 [S,Hkv,ld]")
         _require(nsel is not None and nsel.dtype == torch.int32 and nsel.is_contiguous(), "nsel must be int32 [S]")
-    kv = kv_desc(k, v, seq_lens, page_table, max_seq_len)
-    _require(k_new.shape[0] == kv.num_seqs and k_new.shape[2] == kv.num_kv_heads, "k_new must be [S,n,Hkv,128]")
-    _check(lib().bd_cache_append(ctypes.byref(kv), k_new.data_ptr(), v_new.data_ptr(), k_new.shape[1], _ptr(idx),
+    kv, S, hkv, _ = _kv(k, v, seq_lens, page_table, max_seq_len)
+    _require(k_new.shape[0] == S and k_new.shape[2] == hkv, "k_new must be [S,n,Hkv,128]")
+    _check(lib().bd_cache_append(kv, k_new.data_ptr(), v_new.data_ptr(), k_new.shape[1], _ptr(idx),
                                  idx.shape[2] if idx is not None else 0, _ptr(nsel), _stream()))
 
 
@@ -455,14 +501,13 @@ def bd_top1_ce(student: torch.Tensor, *, teacher: Optional[torch.Tensor] = None,
                  "teacher must be fp32 [R,V]")
     if targets is not None:
         _require(targets.dtype == torch.int32 and targets.shape == (R,) and targets.is_contiguous(), "targets must be int32 [R]")
-    dev = student.device
-    loss = torch.empty((R,), dtype=torch.float32, device=dev)
-    tgt = torch.empty((R,), dtype=torch.int32, device=dev) if return_targets else None
-    lse = torch.empty((R,), dtype=torch.float32, device=dev) if return_lse else None
-    L = lib()
-    wp, wb = _ws("ce", L.bd_top1_ce_workspace_bytes(R, V), dev, workspace)
-    _check(L.bd_top1_ce(student.data_ptr(), student.stride(0), _ptr(teacher), teacher.stride(0) if teacher is not None else 0,
-                        _ptr(targets), R, V, loss.data_ptr(), _ptr(tgt), _ptr(lse), wp, wb, _stream()))
+    loss = student.new_empty((R,))
+    tgt = student.new_empty((R,), dtype=_I32T) if return_targets else None
+    lse = student.new_empty((R,)) if return_lse else None
+    stream = _stream()
+    wp, wb = _ws("ce", _ws_bytes("bd_top1_ce_workspace_bytes", R, V), student, stream, workspace)
+    _check(lib().bd_top1_ce(student.data_ptr(), student.stride(0), _ptr(teacher), teacher.stride(0) if teacher is not None else 0,
+                        _ptr(targets), R, V, loss.data_ptr(), _ptr(tgt), _ptr(lse), wp, wb, stream))
     out = [loss] + ([tgt] if return_targets else []) + ([lse] if return_lse else [])
     return out[0] if len(out) == 1 else tuple(out)
 
