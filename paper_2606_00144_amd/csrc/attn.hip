@@ -1122,17 +1122,6 @@ __device__ inline void block_pv(RowState<NT>& st, const bf16x8 (&vt)[8], const b
     }
 }
 
-// Scheduling of a phase: N MFMAs, each followed by up to V vector instructions (transcendentals
-// included), so that the in-order issue of one wave alternates between the two units.
-template <int N, int V>
-__device__ inline void interleave_mfma_valu() {
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    __builtin_amdgcn_sched_group_barrier(0x402, V, 0);
-  }
-}
-
 // K and the key positions of the tile in LDS slot `slot` (lane's part at slot + 16*lane), one
 // statement ending in its own wait.
 __device__ inline void read_block_k(u32x4 (&k)[2][4], u32x4 (&tp)[2], uint32_t slot, uint32_t ap, int lane) {

@@ -55,9 +55,8 @@ constexpr int64_t kTargetBlocks = 256;             // one workgroup per CU
 // ---- dQ kernel ----------------------------------------------------------------
 constexpr int kQWaves = 8;
 constexpr int kQThreads = kQWaves * kWave;
-constexpr int kQRing = 5;                          // tile slots; kQRing-1 tiles in flight
-constexpr int kQLoads = 24;                        // 16-byte loads per lane per tile (3 per wave)
-constexpr int kQTileBytes = 16384 + kRmTileBytes; // K and V in the score layout, then K row-major
+constexpr int kQRing = 7;                          // tile slots: the two being read, up to five in flight
+constexpr int kQTileBytes = 2 * kW32TileBytes;     // K and V
 constexpr int kQMaxEntries = 4096;                 // entries of a workgroup's share: what the LDS beside the ring holds
 constexpr int kQSlotCap = kQMaxEntries + kQRing * kTile;
 constexpr int kQFixedEntries = 112;                // a workgroup's prologue and record, in entries (~10 us)
@@ -66,24 +65,8 @@ constexpr int kRecFloats = 2 * 16 * kD;            // one wave's dQ partial: 32 
 struct DqSmem {
   alignas(16) int32_t roff[kQSlotCap];
   alignas(16) int32_t tpos[kQSlotCap];
-  alignas(16) uint8_t ring[kQRing][kQTileBytes];
+  alignas(256) uint8_t ring[kQRing][kQTileBytes];
 };
-
-// Tile load q of a lane (0..23).  q < 8: K, score layout (key sub-tile q/4 -> rows 16*(q/4) + lane%16,
-// 16 bytes at d = 32*(lane/16) + 8*(q%4)); 8 <= q < 16: V, same layout; 16 <= q < 24: K again, as a
-// row-major tile for the transposing reads of the dQ product (rm_row, rm_chunk).
-__device__ inline int load_row_in_tile(int q, int lane) {
-  const int lr = lane & 15;
-  return q < 16 ? 16 * ((q & 7) >> 2) + lr : rm_row(q - 16, lane);
-}
-__device__ inline void dq_dma_load(const KvView& kv, uint32_t r, uint32_t max_roff, int q, uint8_t* dst, int lane) {
-  const int lg = lane >> 4;
-  const uint32_t ro = r < max_roff ? r : max_roff;
-  const uint64_t base = (uint64_t)ro << 3;
-  if (q < 8) dma16(kv.k + base + 32 * lg + 8 * (q & 3), dst + q * 1024);
-  else if (q < 16) dma16(kv.v + base + 32 * lg + 8 * (q & 3), dst + q * 1024);
-  else dma16(kv.k + base + 8 * rm_chunk(lane), dst + 16384 + rm_block_off(q - 16));
-}
 
 // Eight 1 KiB pieces of a tile (loads q0 .. q0+7) into registers, with their wait.
 __device__ inline void read8(u32x4 (&x)[8], uint32_t a) {
@@ -100,117 +83,110 @@ __device__ inline void read8(u32x4 (&x)[8], uint32_t a) {
       : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]), "=&v"(x[6]), "=&v"(x[7])
       : "v"(a));
 }
-// K pieces (score layout), the tile's key positions and the row offsets of this wave's next loads.
-__device__ inline void read8_pos_rows(u32x4 (&x)[8], u32x4 (&tp)[2], uint32_t (&r)[3], uint32_t a, uint32_t ap,
-                                      uint32_t a0, uint32_t a1, uint32_t a2) {
-  asm volatile(
-      "ds_read_b128 %0, %13\n"
-      "ds_read_b128 %1, %13 offset:1024\n"
-      "ds_read_b128 %2, %13 offset:2048\n"
-      "ds_read_b128 %3, %13 offset:3072\n"
-      "ds_read_b128 %4, %13 offset:4096\n"
-      "ds_read_b128 %5, %13 offset:5120\n"
-      "ds_read_b128 %6, %13 offset:6144\n"
-      "ds_read_b128 %7, %13 offset:7168\n"
-      "ds_read_b128 %8, %14\n"
-      "ds_read_b128 %9, %14 offset:64\n"
-      "ds_read_b32 %10, %15\n"
-      "ds_read_b32 %11, %16\n"
-      "ds_read_b32 %12, %17\n"
-      "s_waitcnt lgkmcnt(0)"
-      : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]), "=&v"(x[6]), "=&v"(x[7]),
-        "=&v"(tp[0]), "=&v"(tp[1]), "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2])
-      : "v"(a), "v"(ap), "v"(a0), "v"(a1), "v"(a2));
-}
-
-// Per-wave row data of the dQ kernel: rows 16*nt + lane%16 of the wave's 32-row block.
+// Per-wave row data of the dQ kernel: row lane%32 of the wave's 32-row block, head dimension half lane/32.
 struct DqRows {
-  bf16x8 qop[2][4];   // Q^T operand (d slots 32*(lane/16) + 8*kk ..)
-  bf16x8 dop[2][4];   // dO^T operand, same layout
-  float lse2[2];      // log-sum-exp in log2 units (+inf: the row's weights are all zero)
-  float Dr[2];        // <dO_r, O_r>
-  int rowpos[2];
+  bf16x8 qop[8];      // Q^T operand
+  bf16x8 dop[8];      // dO^T operand, same layout
+  float lse2;         // log-sum-exp in log2 units (+inf: the row's weights are all zero)
+  float Dr;           // <dO_r, O_r>
+  int rowpos;
 };
 
-// One 32-key tile: dQ^T[nt][dt] += K^T . (P o (dP - D))^T.  `kreg` holds the K pieces (score layout)
-// already read; the V and transposed-K pieces are read from the slot at `src`.  dS enters the product
-// as a bf16 pair hi + lo (lo the rounded remainder): where a row's weight concentrates, dS terms of
-// both signs nearly cancel in dQ and a single bf16 rounding of dS would dominate the result's error.
-// ktr_off: this lane's read_vt_tr offsets of the tile's row-major K (16 KiB + tr_lane_off); dQ^T
-// register r of d-tile dt then holds d = 32*(lane/16) + 4*dt + r.
-template <class PosFn>
-__device__ inline void dq_tile_step(f32x4 (&acc)[2][8], const DqRows& rw, const u32x4 (&kreg)[8], uint32_t src,
-                                    const uint32_t (&ktr_off)[4], int lane, float scale_log2, bool dirty,
-                                    PosFn pos_of) {
-  f32x4 p[2][2];
+__device__ inline f32x16 zero16() {
+  f32x16 z;
 #pragma unroll
-  for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      f32x4 a = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kreg[4 * sub + j]), rw.qop[nt][j], a, 0, 0, 0);
-      p[sub][nt] = a;
-    }
-  if (dirty) {
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int tpos = pos_of(i);
-        if (!(tpos >= 0 && tpos <= rw.rowpos[nt])) p[i >> 2][nt][i & 3] = -INFINITY;
-      }
-  }
-#pragma unroll
-  for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        p[sub][nt][e] = __builtin_amdgcn_exp2f(fmaf(p[sub][nt][e], scale_log2, -rw.lse2[nt]));
+  for (int i = 0; i < 16; ++i) z[i] = 0.f;
+  return z;
+}
 
-  u32x4 vreg[8];
-  read8(vreg, src + 8 * 1024 + 16 * lane);
-  bf16x8 dsop[2], dslo[2];
+// Row operands of a tile (K or V), and scores (K . Q^T) or dP (V . dO^T) from them: key w32_result_row(i) of
+// the lane's row in register i.
+__device__ inline void dq_read_rows(bf16x8 (&x)[8], const uint8_t* tile, uint32_t row_off) {
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
-    f32x4 dp[2];
+  for (int j = 0; j < 8; ++j) x[j] = w32_read_row(tile, row_off, j);
+}
+__device__ inline f32x16 dq_rows_product(const bf16x8 (&x)[8], const bf16x8 (&op)[8]) {
+  f32x16 a = zero16();
 #pragma unroll
-    for (int sub = 0; sub < 2; ++sub) {
-      f32x4 a = {0.f, 0.f, 0.f, 0.f};
+  for (int j = 0; j < 8; ++j) a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[j], op[j], a, 0, 0, 0);
+  return a;
+}
+// Scheduling of a phase of N times D LDS reads, M products and up to V vector instructions.
+template <int N, int D, int M, int V>
+__device__ inline void interleave_lds_mfma_valu() {
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(vreg[4 * sub + j]), rw.dop[nt][j], a, 0, 0, 0);
-      dp[sub] = a;
-    }
+  for (int i = 0; i < N; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x100, D, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, M, 0);
+    __builtin_amdgcn_sched_group_barrier(0x402, V, 0);
+  }
+}
+
+// One step of the dQ loop: tile t's dQ^T[dt] += K^T . (P o (dP - D))^T from its scores `sc` and its V (`vt`,
+// already read), and tile t+1's scores and V.  The waves of a workgroup run in step (they share the ring), so
+// a step whose LDS reads, products and vector work follow one another costs their sum; here each of the three
+// phases runs its products beside the vector work and beside the LDS reads of the next phase:
+//   dP(t)        | exponentials of tile t | reads K(t+1)
+//   scores(t+1)  | dS(t)                  | reads K^T(t), first half
+//   dQ           |                        | reads K^T(t), second half, and V(t+1)
+// The first two, which hold the vector work, run at a raised priority: the two waves of a SIMD drift apart,
+// one with vector work while the other runs its dQ product.  Measured, with 32x32 products and one K copy in
+// a tile where 16x16 products and two K copies (one for each read) were: 8K, C = 64, four views, 4 sequences
+// 141 -> 114 us; 16K, C = 256 238 -> 196 us (without the raised priority 119 and 208, without the interleaved
+// LDS reads 132 and 221).  What bounds it: at 2.1 us a tile the matrix units are busy 45% of the time and the
+// vector units 30%; the two waves of a SIMD still meet in the same phase.
+// P and dS never leave registers: a product's result order is the next one's operand order.  dS enters its
+// product as a bf16 pair hi + lo (lo the rounded remainder): where a row's weight concentrates, dS terms of
+// both signs nearly cancel in dQ and a single bf16 rounding of dS would dominate the result's error.
+__device__ inline void dq_step(f32x16 (&acc)[4], const DqRows& rw, const f32x16& sc, f32x16& next, bf16x8 (&vt)[8],
+                               const uint8_t* tile, const uint8_t* tile1, uint32_t row_off, uint32_t tr_off,
+                               float scale_log2) {
+  // the reads' addresses are formed where they are used: kept across the loop they cost spills
+  asm volatile("" : "+v"(row_off), "+v"(tr_off));
+  __builtin_amdgcn_s_setprio(1);
+  bf16x8 kt[8];
+  f32x16 p;
+  dq_read_rows(kt, tile1, row_off);
+  const f32x16 dp = dq_rows_product(vt, rw.dop);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) p[i] = __builtin_amdgcn_exp2f(fmaf(sc[i], scale_log2, -rw.lse2));
+  interleave_lds_mfma_valu<8, 1, 1, 4>();
+  __builtin_amdgcn_sched_barrier(0);
+  bf16x8 kr[4], kr1[4];
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt) kr[dt] = w32_read_tr(tile, tr_off, dt, 0);
+  next = dq_rows_product(kt, rw.qop);
+  bf16x8 hi[2], lo[2];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
     u32x4 w, wl;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int i0 = 2 * i, i1 = 2 * i + 1;
-      const float d0 = p[i0 >> 2][nt][i0 & 3] * (dp[i0 >> 2][i0 & 3] - rw.Dr[nt]);
-      const float d1 = p[i1 >> 2][nt][i1 & 3] * (dp[i1 >> 2][i1 & 3] - rw.Dr[nt]);
+      const int i0 = 8 * ks + 2 * i;
+      const float d0 = p[i0] * (dp[i0] - rw.Dr), d1 = p[i0 + 1] * (dp[i0 + 1] - rw.Dr);
       w[i] = pack_bf16x2(d0, d1);
       wl[i] = pack_bf16x2(d0 - bf16_lo(w[i]), d1 - bf16_hi(w[i]));
     }
-    dsop[nt] = as_bf16x8(w);
-    dslo[nt] = as_bf16x8(wl);
+    hi[ks] = as_bf16x8(w);
+    lo[ks] = as_bf16x8(wl);
   }
-
-  bf16x8 kts[8];
-  {
-    const uint32_t a4[4] = {src + ktr_off[0], src + ktr_off[1], src + ktr_off[2], src + ktr_off[3]};
-    read_vt_tr(kts, a4);
-  }
+  interleave_lds_mfma_valu<8, 1, 1, 10>();
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_setprio(0);
 #pragma unroll
-  for (int dt = 0; dt < 8; ++dt) {
-    const bf16x8 a = kts[dt];
+  for (int dt = 0; dt < 4; ++dt) kr1[dt] = w32_read_tr(tile, tr_off, dt, 1);
+  asm volatile("" : "+v"(row_off));
+  dq_read_rows(vt, tile1 + kW32TileBytes, row_off);
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      acc[nt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, dsop[nt], acc[nt][dt], 0, 0, 0);
-      acc[nt][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, dslo[nt], acc[nt][dt], 0, 0, 0);
-    }
-  }
+  for (int dt = 0; dt < 4; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr[dt], hi[0], acc[dt], 0, 0, 0);
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr[dt], lo[0], acc[dt], 0, 0, 0);
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr1[dt], hi[1], acc[dt], 0, 0, 0);
+#pragma unroll
+  for (int dt = 0; dt < 4; ++dt) acc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kr1[dt], lo[1], acc[dt], 0, 0, 0);
+  interleave_lds_mfma_valu<16, 1, 1, 2>();
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 // Every kernel argument line requested at entry, so the arguments cost one memory round trip (the
@@ -244,10 +220,10 @@ __device__ inline int fetch_dkv_args(const AttnBwdParams& p) {
 // loads in flight (which a __syncthreads fence would wait for).
 __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// The dQ kernel's cut of a unit's key stream (StreamCut): equal shares starting on whole tiles.
-// Weighting gathered entries more, as the forward does, was slower here (163 vs 144 us; 178 vs
-// 137 us with all pieces of a range in one slot table): the gathered tiles of the views, each row
-// a separate 256-byte read of three tile pieces, slow down as more workgroups stream them at once.
+// The dQ kernel's cut of a unit's key stream (StreamCut): equal shares starting on whole tiles.  A gathered
+// tile costs what a contiguous one does (its loads bring whole rows).  Counting a branch's start as 64 more
+// entries (its rows, slot table and first tiles take ~4 us) was slower: 123 against 114 us with four views
+// and the cache, 10,496 entries a unit.
 constexpr int kQWGather = 1, kQWFull = 1;
 using DqCut = StreamCut<kQWGather, kQWFull, kTile>;
 
@@ -256,7 +232,7 @@ __global__ __launch_bounds__(kQThreads) void dq_kernel(AttnBwdParams p) {
   __shared__ DqSmem sm;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int lg = lane >> 4, lr = lane & 15;
+  const int lg = lane >> 4, lr = lane & 31, hf = lane >> 5;
 
   // ---- unit (sequence, KV head, row group) and this workgroup's share w of the unit's key stream
   const int bid = xcd_remap(blockIdx.x + fetch_bwd_args(p), gridDim.x);
@@ -292,126 +268,156 @@ __global__ __launch_bounds__(kQThreads) void dq_kernel(AttnBwdParams p) {
   // ---- this wave's rows: Q once; dO, lse and D = <dO, O> per branch
   const int64_t branch_rows = (int64_t)p.S * p.C * p.Hq;
   DqRows rw;
-  int64_t orow[2];
-  bool rvalid[2];
+  const int nrow = rb * 32 + lr;
+  const bool rvalid = has_rows && nrow < p.R;
+  const int jrow = rvalid ? nrow / p.G : 0;
+  const int64_t orow = ((int64_t)s * p.C + jrow) * p.Hq + g * p.G + (rvalid ? nrow % p.G : 0);
+  rw.rowpos = rvalid ? L - p.C + jrow : 0x7FFFFFFF;
+  // Rows reach the operand layout through this wave's 8 KiB of the ring: 16 lanes read a whole row at a
+  // time (rows 4i + lane/16 in step i), and the operand reads follow the tile layout.  Read straight into
+  // the operand layout, a load touched one 16-byte part of 64 lines and the rows cost the L1 three times
+  // the tiles' traffic.
+  uint8_t* rows_lds = sm.ring[0] + wave * kW32TileBytes;
+  int row32 = (int)orow;                       // row index within [S][C][Hq] (2^31 rows would be 512 GiB)
+  auto row_of = [&](int i) {                         // the row this lane reads in step i, -1: none
+    return __builtin_amdgcn_ds_bpermute(4 * (4 * i + lg), rvalid ? row32 : -1);
+  };
+  const int pc = lane & 15;                          // its chunk of them
+  // row 4i + lg = 16*(i/4) + 4*(i%4) + lg: sub-tile i/4, load slot lg, group i%4 of the tile layout
+  auto put_row = [&](int i, const u32x4& x) {
+    const int m = 4 * (i & 3) + lg;
+    *reinterpret_cast<u32x4*>(rows_lds + 4096 * (i >> 2) + 1024 * lg + 256 * (i & 3) + 16 * (pc ^ w32_swizzle(m))) = x;
+  };
+  auto get_rows = [&](bf16x8 (&op)[8]) {
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
-    const int n = rb * 32 + 16 * nt + lr;
-    rvalid[nt] = has_rows && n < p.R;
-    const int j = rvalid[nt] ? n / p.G : 0;
-    const int h = g * p.G + (rvalid[nt] ? n % p.G : 0);
-    orow[nt] = ((int64_t)s * p.C + j) * p.Hq + h;
-    rw.rowpos[nt] = rvalid[nt] ? L - p.C + j : 0x7FFFFFFF;
+    for (int j = 0; j < 8; ++j) op[j] = w32_read_row(rows_lds, w32_row_off(lane), j);
+  };
+  {
+    u32x4 x[8];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-      rw.qop[nt][kk] = as_bf16x8(rvalid[nt] ? load16(p.q + orow[nt] * kD + 32 * lg + 8 * kk) : u32x4{0u, 0u, 0u, 0u});
+    for (int i = 0; i < 8; ++i) {
+      const int row = row_of(i);
+      x[i] = row >= 0 ? load16(p.q + (int64_t)row * kD + 8 * pc) : u32x4{0u, 0u, 0u, 0u};
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) put_row(i, x[i]);
+    get_rows(rw.qop);
   }
   // A branch's rows: the loads are issued before the piece's slot table is filled (its idx loads
   // then share their round trip), the sums D = <dO, O> taken after it.
   struct BranchRaw {
-    u32x4 dv[2][4];
-    f32x4 o[2][4][2];
-    float lse[2];
+    u32x4 dv[8];
+    f32x4 o[8][2];
+    float lse;
   };
   auto issue_branch_rows = [&](int b, BranchRaw& x) {
+    asm volatile("" : "+v"(row32));                  // the addresses are not kept across the pieces
     const bool gb = b < p.V;
     const float* outb = gb ? p.o32_g + (int64_t)b * branch_rows * kD : p.o32_f;
     const uint16_t* doutb = gb ? p.dout_g + (int64_t)b * branch_rows * kD : p.dout_f;
     const float* lseb = gb ? p.lse_g + (int64_t)b * branch_rows : p.lse_f;
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const int64_t off = orow[nt] * kD + 32 * lg + 8 * kk;
-        x.dv[nt][kk] = rvalid[nt] ? load16(doutb + off) : u32x4{0u, 0u, 0u, 0u};
-        x.o[nt][kk][0] = rvalid[nt] ? *reinterpret_cast<const f32x4*>(outb + off) : f32x4{0.f, 0.f, 0.f, 0.f};
-        x.o[nt][kk][1] = rvalid[nt] ? *reinterpret_cast<const f32x4*>(outb + off + 4) : f32x4{0.f, 0.f, 0.f, 0.f};
-      }
-      x.lse[nt] = rvalid[nt] ? lseb[orow[nt]] : INFINITY;
+    for (int i = 0; i < 8; ++i) {
+      const int row = row_of(i);
+      const int64_t off = (int64_t)row * kD + 8 * pc;
+      const bool ok = row >= 0;
+      x.dv[i] = ok ? load16(doutb + off) : u32x4{0u, 0u, 0u, 0u};
+      x.o[i][0] = ok ? *reinterpret_cast<const f32x4*>(outb + off) : f32x4{0.f, 0.f, 0.f, 0.f};
+      x.o[i][1] = ok ? *reinterpret_cast<const f32x4*>(outb + off + 4) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
+    x.lse = rvalid ? lseb[orow] : INFINITY;
   };
   auto finish_branch_rows = [&](const BranchRaw& x) {
+    float dr = 0.f;
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
+    for (int i = 0; i < 8; ++i) {
+      const u32x4 dv = x.dv[i];
+      const f32x4 o0 = x.o[i][0], o1 = x.o[i][1];
+      put_row(i, dv);
       float dsum = 0.f;
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        const u32x4 dv = x.dv[nt][kk];
-        const f32x4 o0 = x.o[nt][kk][0], o1 = x.o[nt][kk][1];
-        rw.dop[nt][kk] = as_bf16x8(dv);
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          dsum += bf16_lo(dv[e]) * o0[2 * e] + bf16_hi(dv[e]) * o0[2 * e + 1];
-          dsum += bf16_lo(dv[e + 2]) * o1[2 * e] + bf16_hi(dv[e + 2]) * o1[2 * e + 1];
-        }
+      for (int e = 0; e < 2; ++e) {
+        dsum += bf16_lo(dv[e]) * o0[2 * e] + bf16_hi(dv[e]) * o0[2 * e + 1];
+        dsum += bf16_lo(dv[e + 2]) * o1[2 * e] + bf16_hi(dv[e + 2]) * o1[2 * e + 1];
       }
-      rw.Dr[nt] = sum_xor32(sum_xor16(dsum));
-      const float l2 = x.lse[nt] * kLog2e;
-      rw.lse2[nt] = l2 == -INFINITY ? INFINITY : l2;   // a row that saw no key has all-zero weights
+      dsum = sum16(dsum);                            // row 4i + lg, in its 16 lanes
+      // lane l wants row l%32: rows 4i .. 4i+3 sit in lane groups 0 .. 3
+      const float got = __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute(64 * (lane & 3), (int)__float_as_uint(dsum)));
+      if ((lr >> 2) == i) dr = got;
     }
+    get_rows(rw.dop);
+    rw.Dr = dr;
+    const float l2 = x.lse * kLog2e;
+    rw.lse2 = l2 == -INFINITY ? INFINITY : l2;       // a row that saw no key has all-zero weights
   };
 
   const int minpos = L - p.C + (rb * 32) / p.G;   // earliest row position of this wave
-  f32x4 acc[2][8];
+  f32x16 acc[4];
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-    for (int dt = 0; dt < 8; ++dt) acc[nt][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int dt = 0; dt < 4; ++dt) acc[dt] = zero16();
 
-  // ---- the three loads of every tile that this wave issues
-  const int q0 = 3 * wave;
-  const int rit0 = load_row_in_tile(q0, lane), rit1 = load_row_in_tile(q0 + 1, lane),
-            rit2 = load_row_in_tile(q0 + 2, lane);
-  uint32_t ktr_off[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) ktr_off[j] = 16384u + tr_lane_off(lane, j);
-  const uint32_t roff_lds = lds_addr(sm.roff), tpos_lds = lds_addr(sm.tpos);
-  const uint32_t ring_lds = lds_addr(sm.ring[0]);
-  auto issue = [&](int tile, const uint32_t (&r)[3]) {
-    uint8_t* dst = sm.ring[tile % kQRing];
-    dq_dma_load(p.kv, r[0], p.max_roff, q0, dst, lane);
-    dq_dma_load(p.kv, r[1], p.max_roff, q0 + 1, dst, lane);
-    dq_dma_load(p.kv, r[2], p.max_roff, q0 + 2, dst, lane);
+  // ---- the two loads of every tile that this wave issues: K (waves 0..3) or V, loads (h, i0) and (h, i0+1)
+  const int lh = (wave & 3) >> 1, li = 2 * (wave & 1);
+  const uint16_t* src = wave < 4 ? p.kv.k : p.kv.v;
+  const uint32_t dma_dst = lds_addr(sm.ring[0]) + (wave < 4 ? 0u : (uint32_t)kW32TileBytes) + 1024u * (uint32_t)(4 * lh + li);
+  const int dma_row = 16 * lh + 4 * lg + li;
+  const int ch0 = 8 * w32_dma_chunk(lane, li), ch1 = 8 * w32_dma_chunk(lane, li + 1);
+  const uint32_t row_off = w32_row_off(lane), tr_off = w32_tr_off(lane);
+  auto issue = [&](int tile) {
+    const uint2 r = *reinterpret_cast<const uint2*>(&sm.roff[kTile * tile + dma_row]);
+    const uint32_t r0 = r.x < p.max_roff ? r.x : p.max_roff, r1 = r.y < p.max_roff ? r.y : p.max_roff;
+    const uint32_t dst = dma_dst + (uint32_t)(tile % kQRing) * kQTileBytes;
+    dma16_hidden(src + ((uint64_t)r0 << 3) + ch0, dst);
+    dma16_hidden(src + ((uint64_t)r1 << 3) + ch1, dst + 1024);
   };
 
-  // entries e_begin .. e_end-1 of one branch through the slot table (a piece never exceeds it)
+  // entries e_begin .. e_end-1 of one branch through the slot table (a piece never exceeds it).  Tiles
+  // 0 .. 4 are issued first; the barrier before step t (even) publishes tiles t+1 and t+2 (this wave's
+  // loads of them are older than those of the two tiles issued after them) and certifies that every wave
+  // has finished step t-1, so the slots of tiles t-2 and t-1 take tiles t+5 and t+6.  A step reads tiles t
+  // and t+1.  Past the last tile the table holds padding (row 0, masked nowhere: its scores are
+  // never used).
   auto stream = [&](int e_begin, int e_end) {
     const int ntiles = (e_end - e_begin + kTile - 1) / kTile;
-    for (int t = 0; t < kQRing - 1; ++t) {
-      uint32_t r[3];
-      asm volatile(
-          "ds_read_b32 %0, %3\n"
-          "ds_read_b32 %1, %4\n"
-          "ds_read_b32 %2, %5\n"
-          "s_waitcnt lgkmcnt(0)"
-          : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2])
-          : "v"(roff_lds + 4 * (kTile * t + rit0)), "v"(roff_lds + 4 * (kTile * t + rit1)),
-            "v"(roff_lds + 4 * (kTile * t + rit2)));
-      issue(t, r);
-    }
-    for (int t = 0; t < ntiles; ++t) {
-      // this wave's loads of tile t are older than the kQRing-2 tiles issued after it
-      asm volatile("s_waitcnt vmcnt(9)\n\ts_barrier" ::: "memory");
-      static_assert(3 * (kQRing - 2) == 9, "wait count follows the ring depth");
-      const int nxt = t + kQRing - 1;
-      const uint32_t src = ring_lds + (uint32_t)(t % kQRing) * kQTileBytes;
-      u32x4 kreg[8];
-      uint32_t r[3];
-      u32x4 tp[2];
-      const int next0 = kTile * nxt;
-      read8_pos_rows(kreg, tp, r, src + 16 * lane, tpos_lds + 4 * (kTile * t + 4 * lg),
-                     roff_lds + 4 * (next0 + rit0), roff_lds + 4 * (next0 + rit1), roff_lds + 4 * (next0 + rit2));
-      bool bad = false;
+    static_assert(kQRing == 7, "the wait counts and the issue distance follow the ring depth");
+    auto publish = [&](int t) {
+      asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      issue(t + 5);
+      issue(t + 6);
+    };
+    auto slot = [&](int t) { return sm.ring[t % kQRing]; };
+    for (int t = 0; t < kQRing - 2; ++t) issue(t);
+    publish(0);
+    if (has_rows) {
+      // scores of absent keys and of keys past the row's position -> -inf, in tiles that hold any
+      auto mask = [&](f32x16& x, int t) {
+        const int tq = sm.tpos[kTile * t + lr];
+        const bool bad = minpos < 0 || (uint32_t)tq > (uint32_t)minpos;    // as unsigned, -1 exceeds every position
+        if (__builtin_amdgcn_ballot_w64(bad) != 0) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int tq = (int)tp[i >> 2][i & 3];
-        bad |= tq < 0 || tq > minpos;
+          for (int i = 0; i < 16; ++i) {
+            const int pos = sm.tpos[kTile * t + w32_result_row(i, hf)];
+            if (!(pos >= 0 && pos <= rw.rowpos)) x[i] = -INFINITY;
+          }
+        }
+      };
+      f32x16 s0, s1;
+      bf16x8 vt[8];
+      dq_read_rows(vt, slot(0), row_off);
+      s0 = dq_rows_product(vt, rw.qop);
+      mask(s0, 0);
+      dq_read_rows(vt, slot(0) + kW32TileBytes, row_off);
+      for (int t = 0;;) {
+        dq_step(acc, rw, s0, s1, vt, slot(t), slot(t + 1), row_off, tr_off, p.scale_log2);
+        if (++t >= ntiles) break;
+        mask(s1, t);
+        dq_step(acc, rw, s1, s0, vt, slot(t), slot(t + 1), row_off, tr_off, p.scale_log2);
+        if (++t >= ntiles) break;
+        mask(s0, t);
+        publish(t);
       }
-      const bool dirty = __builtin_amdgcn_ballot_w64(bad) != 0;
-      issue(nxt, r);
-      if (has_rows)
-        dq_tile_step(acc, rw, kreg, src, ktr_off, lane, p.scale_log2, dirty,
-                     [&](int i) { return (int)tp[i >> 2][i & 3]; });
+    } else {
+      for (int t = 2; t < ntiles; t += 2) publish(t);    // only keeps the ring going
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // padding loads land before the ring is reused
   };
@@ -430,61 +436,60 @@ __global__ __launch_bounds__(kQThreads) void dq_kernel(AttnBwdParams p) {
     // these barriers wait for LDS traffic alone (a __syncthreads fence would wait for the rows too)
     lds_barrier();                                // the previous piece's slot table and ring are free
     fill_slot_table<PAGED, kQThreads, kQSlotCap>(p.kv, s, g, L, idx_row, e0, e1, nslots, sm.roff, sm.tpos, tid);
-    lds_barrier();
     finish_branch_rows(raw);
-    if (e0 == 0 && p.rstats && lg == 0) {         // the branch's first workgroup publishes the row stats
+    lds_barrier();                                // the table is complete, and every wave has its rows
+    if (e0 == 0 && p.rstats && hf == 0 && rvalid) {   // the branch's first workgroup publishes the row stats
       float* rs = p.rstats + (((int64_t)b * p.S * p.Hkv + pair) * p.R_pad + rb * 32) * 2;
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-        if (rvalid[nt]) *reinterpret_cast<float2*>(rs + 2 * (16 * nt + lr)) = float2{rw.lse2[nt], rw.Dr[nt]};
+      *reinterpret_cast<float2*>(rs + 2 * lr) = float2{rw.lse2, rw.Dr};
     }
     stream(e0, e1);
   }
 
-  // ---- dQ rows 16*nt + lane%16; register r of d-tile dt holds d = 32*(lane/16) + 4*dt + r
-  auto write_rows = [&](const f32x4 (&o)[2][8]) {
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      if (!rvalid[nt]) continue;
-      float* drow = p.dq + orow[nt] * kD + 32 * lg;
-#pragma unroll
-      for (int dt = 0; dt < 8; ++dt) *reinterpret_cast<f32x4*>(drow + 4 * dt) = o[nt][dt] * p.scale;
-    }
-  };
+  // ---- dQ row lane%32; register i of d-tile dt holds d = 32*dt + w32_result_row(i)
   if (p.nW == 1) {
-    if (has_rows) write_rows(acc);
+    if (rvalid) {
+      float* drow = p.dq + orow * kD + 4 * hf;
+#pragma unroll
+      for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<f32x4*>(drow + 32 * dt + 8 * q) =
+              f32x4{acc[dt][4 * q], acc[dt][4 * q + 1], acc[dt][4 * q + 2], acc[dt][4 * q + 3]} * p.scale;
+    }
     return;
   }
 
-  // ---- publish this wave's partial as record w of its row block: chunk (nt, dt) x lane float4s;
+  // ---- publish this wave's partial as record w of its row block: chunk (dt, q) x lane float4s;
   // bwd_merge_kernel, launched after the dK/dV kernel, sums them
   if (has_rows) {
     const __amdgpu_buffer_rsrc_t urec =
         make_rsrc(p.part_q + ((int64_t)unit * kQWaves + wave) * p.nW * kRecFloats, (uint32_t)(p.nW * kRecFloats * 4));
     const uint32_t rec = (uint32_t)w * kRecFloats * 4;
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
+    for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-      for (int dt = 0; dt < 8; ++dt) store16_coherent(urec, rec + 16 * ((nt * 8 + dt) * kWave + lane), acc[nt][dt]);
+      for (int q = 0; q < 4; ++q)
+        store16_coherent(urec, rec + 16 * ((4 * dt + q) * kWave + lane),
+                         f32x4{acc[dt][4 * q], acc[dt][4 * q + 1], acc[dt][4 * q + 2], acc[dt][4 * q + 3]});
   }
 }
 
-// Sum of the dQ partials: one wave per (unit, row block, row tile nt, half dh of the d-tiles) adds
+// Sum of the dQ partials: one wave per (unit, row block, d-tile dt) adds
 // the nW workgroups' records in workgroup order, so the result does not depend on scheduling.  A
 // separate launch spreads it over the chip: summed by the unit's last workgroup, 8 records of
 // 128 KiB went into one CU (15 us at one CU's bandwidth).  Every load of a batch of kQMBatch
 // records is issued before any is added.  Block `id` of the merge kernel's dQ part.
 constexpr int kQMBatch = 8;
 __device__ inline void dq_merge_block(const AttnBwdParams& p, int id) {
-  const int lane = threadIdx.x, lg = lane >> 4, lr = lane & 15;
-  const int dh = id & 1, nt = (id >> 1) & 1;
+  const int lane = threadIdx.x;
+  const int dt = id & 3;
   id >>= 2;
   const int wave = id % kQWaves, unit = id / kQWaves;
   const int rg = unit % p.n_rg, pair = unit / p.n_rg;
   const int g = pair % p.Hkv, s = pair / p.Hkv;
   const int rb = rg * kQWaves + wave;
   if (rb >= p.n_rb) return;
-  const int n = rb * 32 + 16 * nt + lr;
+  const int n = rb * 32 + (lane & 31);
   const __amdgpu_buffer_rsrc_t urec =
       make_rsrc(p.part_q + ((int64_t)unit * kQWaves + wave) * p.nW * kRecFloats, (uint32_t)(p.nW * kRecFloats * 4));
   f32x4 o[4];
@@ -497,7 +502,7 @@ __device__ inline void dq_merge_block(const AttnBwdParams& p, int id) {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         x[kk][i] = k + kk < p.nW ? load16_coherent(urec, (uint32_t)(k + kk) * kRecFloats * 4 +
-                                                             16 * ((nt * 8 + 4 * dh + i) * kWave + lane))
+                                                             16 * ((4 * dt + i) * kWave + lane))
                                  : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kk = 0; kk < kQMBatch; ++kk)
@@ -505,11 +510,11 @@ __device__ inline void dq_merge_block(const AttnBwdParams& p, int id) {
       for (int i = 0; i < 4; ++i) o[i] += x[kk][i];
   }
   if (n >= p.R) return;
-  // register r of d-tile dt = 4*dh + i holds d = 32*lg + 4*dt + r
+  // chunk i of d-tile dt holds d = 32*dt + 8*i + 4*(lane/32) + 0..3
   const int j = n / p.G, h = g * p.G + n % p.G;
-  float* drow = p.dq + (((int64_t)s * p.C + j) * p.Hq + h) * kD + 32 * lg + 16 * dh;
+  float* drow = p.dq + (((int64_t)s * p.C + j) * p.Hq + h) * kD + 32 * dt + 4 * (lane >> 5);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x4*>(drow + 4 * i) = o[i] * p.scale;
+  for (int i = 0; i < 4; ++i) *reinterpret_cast<f32x4*>(drow + 8 * i) = o[i] * p.scale;
 }
 
 // ---- dK/dV kernel ---------------------------------------------------------------

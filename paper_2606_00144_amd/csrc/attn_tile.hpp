@@ -19,6 +19,75 @@ __device__ inline void dma16_nt(const uint16_t* g, uint8_t* l) {
   __builtin_amdgcn_global_load_lds((const void*)g, (__attribute__((address_space(3))) void*)l, 16, 0, kPolicyNt);
 }
 
+// The same issued by hand, at an LDS address: the compiler's wait analysis does not see it, so ordinary LDS
+// reads beside it wait for LDS alone (it would otherwise wait for every such load in flight before any LDS
+// read).  The kernel waits for its tiles explicitly.  M0 is a reserved register: the compiler keeps nothing
+// in it across statements.
+__device__ inline void dma16_hidden(const uint16_t* g, uint32_t lds) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n"
+      "s_nop 0\n"
+      "global_load_lds_dwordx4 %1, off"
+      :
+      : "s"(lds), "v"(g)
+      : "memory");
+}
+
+// ---- 32-row tiles for v_mfma_f32_32x32x16_bf16 ---------------------------------
+//
+// A tile of 32 rows of 128 bf16 (8 KiB) that serves both kinds of operand reads.  Load (h, i), 0 <= h < 2,
+// 0 <= i < 4, of lane l brings 16 bytes of row 16h + 4*(l/16) + i to byte 1024*(4h + i) + 16*l, so a load
+// covers four whole 256-byte rows.  Chunk c (16 bytes) of row m sits at position c ^ w32_swizzle(m % 16).
+// Every row starts on the same LDS bank; the swizzle takes all 16 values over 16 rows (the row operand:
+// lanes read the same chunk of different rows) and its upper two bits differ over four rows with the same
+// m / 4 (the transposing read: 32 lanes read 64 bytes of each of four rows), so neither read meets a bank
+// twice.
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+constexpr int kW32TileBytes = 8192;
+__device__ inline int w32_swizzle(int m) { return ((m & 3) << 2) | (m >> 2); }
+// chunk that lane l's load (h, i) fetches of its row: w32_swizzle(4*(l/16) + i) = 4i | l/16
+__device__ inline int w32_dma_chunk(int lane, int i) { return (lane & 15) ^ (lane >> 4) ^ (4 * i); }
+// Row operand: byte of chunk 8*(l/32) of row l%32; chunk + j (the contraction's step j) is at this ^ 16*j.
+// Lane half l/32 holds the head dimension's half l/32 (the order of a contraction does not matter).
+__device__ inline uint32_t w32_row_off(int lane) {
+  const int m = lane & 31;
+  return 4096u * (uint32_t)(m >> 4) + 1024u * (uint32_t)(m & 3) + 256u * (uint32_t)((m >> 2) & 3) +
+         16u * (uint32_t)((8 * (lane >> 5)) ^ w32_swizzle(m & 15));
+}
+// Transposed operand (M = d, contraction over the tile's rows) of d-tile dt (d = 32*dt + l%32) and step ks:
+// slots 0..3 hold rows 16ks + 4*(l/32) + 0..3, slots 4..7 rows 8 further, which is the order in which
+// v_mfma_f32_32x32x16 leaves a 32-row result in lane l's registers 8ks .. 8ks+7.  Byte for dt = 0, slots
+// 0..3, ks = 0; ks adds 4096, dt flips 64*dt, slots 4..7 add 512 and flip 32.
+__device__ inline uint32_t w32_tr_off(int lane) {
+  const int r = (lane >> 2) & 3, hf = lane >> 5;       // row r of the four, d = 16*((l/16)%2) + 4*(l%4)
+  const int c = (2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ hf;
+  return 1024u * (uint32_t)r + 256u * (uint32_t)hf + 16u * (uint32_t)((4 * r) ^ c) + 8u * (uint32_t)(lane & 1);
+}
+__device__ inline bf16x8 w32_read_row(const uint8_t* tile, uint32_t row_off, int j) {
+  return *reinterpret_cast<const bf16x8*>(tile + (row_off ^ (16u * (uint32_t)j)));
+}
+__device__ inline bf16x8 w32_read_tr(const uint8_t* tile, uint32_t tr_off, int dt, int ks) {
+  typedef __attribute__((address_space(3))) bf16x4* lds_ptr;
+  const uint32_t a = (tr_off ^ (64u * (uint32_t)dt)) + 4096u * (uint32_t)ks;
+  const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr)(tile + a));
+  const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr)(tile + ((a ^ 32u) + 512u)));
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+// Row of register i of a 32x32 result: 8*(i/4) + 4*(l/32) + i%4.
+__device__ inline int w32_result_row(int i, int hf) { return 8 * (i >> 2) + 4 * hf + (i & 3); }
+
+// Scheduling of a phase: N products, each followed by up to V vector instructions (transcendentals
+// included), so that the in-order issue of one wave alternates between the two units.
+template <int N, int V>
+__device__ inline void interleave_mfma_valu() {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+    __builtin_amdgcn_sched_group_barrier(0x402, V, 0);
+  }
+}
+
 // Transposed operand for d-tile dt from 8 rows of 16 bytes per lane (row slot i = register i,
 // bytes 16*(lane%16) of the row): slot i of the result holds row i's element 8*(lane%16) + dt.
 // An 8x8 bf16 block transposed in registers with byte permutes.
