@@ -368,7 +368,31 @@ __device__ inline void unpack_record_bf16(const u32x4& w, f32x4& a, f32x4& b) {
 // per launch when some unit has more than kMergeGroup splits; the one-level merge keeps its own code).
 constexpr int kMergeGroup = 8;
 
-template <int NT, bool PAGED, bool TWO_LEVEL>
+// The sequence of rank r (0: the longest, ties in index order) among S <= 64, and its length entry.  Each
+// lane holds one sequence's length; the r-th largest value is found bit by bit with ballots.
+__device__ inline int nth_longest(const int32_t* seq_lens, int S, int max_seq_len, int r, int& raw) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int mine = lane < S ? seq_lens[lane] : 0;
+  const int len = lane < S ? (mine < 0 ? 0 : (mine > max_seq_len ? max_seq_len : mine)) : -1;
+  int v = 0;
+  for (int bit = 31 - __builtin_clz(max_seq_len | 1); bit >= 0; --bit) {
+    const int cand = v | (1 << bit);
+    if (__builtin_popcountll(__builtin_amdgcn_ballot_w64(len >= cand)) > r) v = cand;
+  }
+  const int above = __builtin_popcountll(__builtin_amdgcn_ballot_w64(len > v));
+  const uint64_t eq = __builtin_amdgcn_ballot_w64(len == v);
+  const int before = __builtin_amdgcn_mbcnt_hi((uint32_t)(eq >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)eq, 0u));
+  const uint64_t hit = __builtin_amdgcn_ballot_w64(len == v && before == r - above);
+  const int s = __builtin_ctzll(hit);              // r < S: some lane has this rank
+  raw = __builtin_amdgcn_readlane(mine, s);
+  return s;
+}
+
+// BY_LENGTH (whole units of the full branch, more of them than CUs): the workgroups start in index order and
+// take the longest sequences first, each one's heads over all XCDs.  A variant of its own: as a run-time
+// branch it put the length's round trip ahead of the query rows' in every launch (verify at 16K x 8: 84.8 ->
+// 88.8 us).
+template <int NT, bool PAGED, bool TWO_LEVEL, bool BY_LENGTH>
 __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p) {
   using RB = RowBlock<NT>;
   __shared__ AttnSmem<NT> sm;
@@ -377,8 +401,9 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p) {
   const int lg = lane >> 4, lr = lane & 15;
 
   // ---- which (kind, unit, split) this workgroup owns
-  const int bid = xcd_remap(blockIdx.x + fetch_args<PAGED>(p), p.nblk);
-  const bool gather = bid < p.nblk_g;
+  const int block = blockIdx.x + fetch_args<PAGED>(p);
+  const int bid = BY_LENGTH ? block : xcd_remap(block, p.nblk);
+  const bool gather = !BY_LENGTH && bid < p.nblk_g;
   const int local = gather ? bid : bid - p.nblk_g;
   const int nsplit = gather ? p.nsplit_g : p.nsplit_f;
   const int kps = gather ? p.kps_g : p.kps_f;
@@ -390,13 +415,14 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p) {
   const int vs = div_small(pair, p.Hkv);     // gather: view*S + s; full: s
   const int g = pair - vs * p.Hkv;
   const int view = gather ? div_small(vs, p.S) : 0;
-  const int s = vs - view * p.S;
+  int s = vs - view * p.S, L_first = 0;
+  if constexpr (BY_LENGTH) s = nth_longest(p.kv.seq_lens, p.S, p.kv.max_seq_len, s, L_first);
   const int unit = gather ? pair * p.n_rb + rb : p.units_g + pair * p.n_rb + rb;
 
   // ---- prologue: every load it needs (cache length, entry count, query rows, the split's idx
   // entries) is issued before any of them is used, so they share one memory round trip
-  const int L_raw = p.kv.seq_lens[s];
-  const int n_raw = *(gather ? p.nsel + vs : p.kv.seq_lens + s);
+  const int L_raw = BY_LENGTH ? L_first : p.kv.seq_lens[s];
+  const int n_raw = BY_LENGTH ? L_first : *(gather ? p.nsel + vs : p.kv.seq_lens + s);
   const int32_t* idx_row = gather ? p.idx + ((int64_t)vs * p.Hkv + g) * p.ld_idx : nullptr;
   // query rows of this lane: row n = rb*RB + 16*nt + lane%16
   bf16x8 qop[NT][4];
@@ -1806,6 +1832,11 @@ AttnPlan plan_attn(int S, int Hkv, int Hq, int nq, int num_views, int ld_idx, in
   pl.nsplit_f = max_L > 0 ? (int)((max_L + kf - 1) / kf) : 1;
   blocks = (int64_t)pl.units_g * pl.nsplit_g + (int64_t)pl.units_f * pl.nsplit_f;
   pl.nblk = blocks > INT32_MAX ? -1 : (int)blocks;
+  // Whole units in more than one round of the CUs (no splits, no counters): the longest sequences first, so
+  // that the last round holds the shortest, and every sequence over all XCDs.  In index order an XCD took a
+  // run of sequences, and the ones with the longest finished last (64 ragged MHA sequences of 4K-16K in 16-row
+  // pages: 1526 -> 1478 us).  Up to 64 sequences, one a lane; within one round the order does not matter.
+  pl.by_length = pl.units_g == 0 && pl.nsplit_f == 1 && pl.units_f > kTargetBlocks && S >= 2 && S <= kWave;
   // group counters per unit for the two-level merge (units of more than kMergeGroup splits)
   auto groups = [](int n) { return n > kMergeGroup ? (n + kMergeGroup - 1) / kMergeGroup : 0; };
   const int gg = pl.units_g ? groups(pl.nsplit_g) : 0, gf = pl.units_f ? groups(pl.nsplit_f) : 0;
@@ -1817,9 +1848,11 @@ AttnPlan plan_attn(int S, int Hkv, int Hq, int nq, int num_views, int ld_idx, in
 }
 
 template <int NT, bool PAGED>
-static hipError_t launch_nt(const AttnParams& p, int nblocks, bool two_level, hipStream_t stream) {
-  if (two_level) hipLaunchKernelGGL((attn_kernel<NT, PAGED, true>), dim3(nblocks), dim3(kThreads), 0, stream, p);
-  else hipLaunchKernelGGL((attn_kernel<NT, PAGED, false>), dim3(nblocks), dim3(kThreads), 0, stream, p);
+static hipError_t launch_nt(const AttnParams& p, const AttnPlan& pl, hipStream_t stream) {
+  const dim3 grid(pl.nblk), block(kThreads);
+  if (pl.ngrp > 0) hipLaunchKernelGGL((attn_kernel<NT, PAGED, true, false>), grid, block, 0, stream, p);
+  else if (pl.by_length) hipLaunchKernelGGL((attn_kernel<NT, PAGED, false, true>), grid, block, 0, stream, p);
+  else hipLaunchKernelGGL((attn_kernel<NT, PAGED, false, false>), grid, block, 0, stream, p);
   return hipGetLastError();
 }
 
@@ -1845,10 +1878,8 @@ hipError_t launch_attn(const AttnParams& args, const AttnPlan& pl, bool paged, h
     }
     return hipGetLastError();
   }
-  const bool two = pl.ngrp > 0;
-  if (pl.nt == 1)
-    return paged ? launch_nt<1, true>(p, pl.nblk, two, stream) : launch_nt<1, false>(p, pl.nblk, two, stream);
-  return paged ? launch_nt<2, true>(p, pl.nblk, two, stream) : launch_nt<2, false>(p, pl.nblk, two, stream);
+  if (pl.nt == 1) return paged ? launch_nt<1, true>(p, pl, stream) : launch_nt<1, false>(p, pl, stream);
+  return paged ? launch_nt<2, true>(p, pl, stream) : launch_nt<2, false>(p, pl, stream);
 }
 
 size_t attn_ws_bytes(int S, int Hkv, int Hq, int nq, int num_views, int ld_idx, int max_L, bool with_full,

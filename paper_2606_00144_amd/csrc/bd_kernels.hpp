@@ -55,6 +55,7 @@ struct AttnPlan {
   int units_g, units_f, nblk;
   int ngrp;                 // group counters per unit of the two-level split merge (0: none)
   bool page_arith;          // paged full branch through the table of page offsets (pages of 16k rows)
+  bool by_length;           // workgroups take the sequences from the longest to the shortest (whole units)
   int units, nbr, nW;       // block mode: (s, g, row group) units, branches, workgroups per unit
   size_t counter_bytes, record_bytes, ws_bytes;
 };

@@ -8,9 +8,10 @@ import numpy as np
 import pytest
 import torch
 
+import oracle as O
 import paper_2606_00144_amd as bd
 import synth
-from gpu_utils import bf16_dev, case, check_selection, i32_dev, oracle_scores, paged_kv
+from gpu_utils import assert_close, bf16_dev, bf16_host64, case, check_selection, i32_dev, oracle_scores, paged_kv
 from mv_check import _rand_bits, _run
 
 pytestmark = pytest.mark.gpu
@@ -85,3 +86,25 @@ def test_select_split_rounds(S, Hkv):
     lens = [520 + 7 * (s % 5) for s in range(S)]
     q, ks = _select_inputs(lens, Hkv, 8, 4, 43)
     _select_case(q, ks, lens, Hkv, 8, 4, 96, "contiguous")
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("S,Hkv", [(64, 5), (9, 32), (65, 4), (2, 160)])
+def test_verify_longest_first(S, Hkv, paged):
+    # more whole units than CUs: up to 64 sequences are taken from the longest to the shortest (65 are not);
+    # equal lengths, the shortest possible and the longest among them
+    gamma, Lmax, Hq = 2, 150, Hkv
+    g = np.random.default_rng(47)
+    lens = [int(n) for n in g.choice([gamma + 1, 40, 97, 98, 150], S)]
+    k, v = _rand_bits((S, Hkv, Lmax, 128), 48), _rand_bits((S, Hkv, Lmax, 128), 49)
+    q = _rand_bits((S, gamma + 1, Hq, 128), 50)
+    case(f"verify longest first S={S} Hkv={Hkv} paged={paged}")
+    if paged:
+        n = (Lmax + 15) // 16
+        table = g.permutation(S * n).reshape(S, n).astype(np.int32)
+        kd, vd = paged_kv(list(k), list(v), table, S * n, 16)
+        out = bd.bd_verify_attn(kd, vd, bf16_dev(q), i32_dev(lens), page_table=i32_dev(table), max_seq_len=Lmax)
+    else:
+        out = bd.bd_verify_attn(bf16_dev(k), bf16_dev(v), bf16_dev(q), i32_dev(lens))
+    torch.cuda.synchronize()
+    assert_close(bf16_host64(out), O.verify_attn(k, v, q, lens, gamma)[0], f"longest first S={S}")
