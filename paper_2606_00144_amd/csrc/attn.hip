@@ -1169,7 +1169,7 @@ __device__ inline void read_block_k(u32x4 (&k)[2][4], u32x4 (&tp)[2], uint32_t s
       : "v"(at), "v"(ap));
 }
 
-// The transposing V reads of read_vt_tr split in two: issue_vt_tr starts them without waiting, so they
+// The transposing V reads split in two: issue_vt_tr starts them without waiting, so they
 // run under the MFMA and VALU work that follows; wait_vt_tr waits for them and unpacks the operands.
 // The raw registers pass from one statement to the other as in-out operands, so nothing reads them
 // before the wait.
@@ -1339,7 +1339,7 @@ __global__ __launch_bounds__(kBThreads) void block_kernel(AttnParams p) {
   const int q0 = 2 * wave, q1 = 2 * wave + 1;
   auto row_in_tile = [&](int q) { return q < 8 ? 16 * (q >> 2) + lr : rm_row(q - 8, lane); };
   const int rit0 = row_in_tile(q0), rit1 = row_in_tile(q1);
-  // transposing V reads (read_vt_tr) of the row-major V half of a tile
+  // transposing reads of the row-major V half of a tile
   uint32_t vtr_off[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) vtr_off[j] = 8192u + tr_lane_off(lane, j);

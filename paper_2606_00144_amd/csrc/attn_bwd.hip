@@ -873,7 +873,7 @@ hipError_t launch_attn_bwd(const AttnBwdParams& p, const AttnBwdPlan& pl, bool p
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  // (unit, row block, row tile, d half) waves for dQ when the workgroups' partials need a sum;
+  // (unit, row block, d-tile) waves for dQ when the workgroups' partials need a sum;
   // (pair, 16-byte column block) waves for dK/dV when more than one branch contributes
   const int64_t nq = pl.nblk_q > 0 && pl.nW > 1 ? (int64_t)pl.units * kQWaves * 4 : 0;
   const int64_t nkv = pl.nblk_kv > 0 && pl.nbr > 1

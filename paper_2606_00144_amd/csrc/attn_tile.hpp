@@ -119,52 +119,21 @@ __device__ inline uint32_t rm_block_off(int q) {
 }
 __device__ inline int rm_row(int q, int lane) { return 4 * q + (lane >> 4); }
 __device__ inline int rm_chunk(int lane) { return (lane & 15) ^ (lane >> 4); }
-// This lane's read_vt_tr addresses relative to such a tile: rows 4*(lane/16) + (lane%16)/4 (k-slots
+// This lane's transposing-read addresses relative to such a tile: rows 4*(lane/16) + (lane%16)/4 (k-slots
 // 0..3; +kRmHighRows for 4..7), d from 32*(lane%4) + 8*j, at the swizzled chunk position.
 __device__ inline uint32_t tr_lane_off(int lane, int j) {
   const int lg = lane >> 4, lr = lane & 15;
   return rm_block_off(lg) + 256u * (uint32_t)(lr >> 2) + 16u * (uint32_t)((4 * (lr & 3) + j) ^ (lr >> 2));
 }
 
-// Transposed operands (V^T in the forward, K^T in the dQ product) of all 8 d-tiles straight from a
-// row-major tile of 32 key rows in LDS with the transposing read ds_read_b64_tr_b16.  Within each
-// 16-lane group that read hands lane i, element j, element i%4 of the 8 bytes that lane 4j + i/4
-// addressed.  The caller passes a[j] = tile + tr_lane_off(lane, j) (d-tiles 2j and 2j+1, k-slots
-// 0..3); +8 selects the odd d-tile, +kRmHighRows (4128) the k-slots 4..7 (tile rows 16..31).  Result vt[dt],
-// slot k of lane l: row[key slot 16*(k/4) + 4*(l/16) + k%4][d = 32*((l%16)/4) + 4*dt + l%4], so
-// accumulator register r of d-tile dt in lane l holds d = 32*(l/16) + 4*dt + r.  One statement,
-// ending in its own wait (direct-to-LDS loads in flight must not make it wait for them).
-static_assert(kRmHighRows == 4128, "the read offsets below are kRmHighRows and kRmHighRows + 8");
-__device__ inline void read_vt_tr(bf16x8 (&vt)[8], const uint32_t (&a)[4]) {
-  uint64_t x[16];
-  asm volatile(
-      "ds_read_b64_tr_b16 %0, %16\n"
-      "ds_read_b64_tr_b16 %1, %16 offset:4128\n"
-      "ds_read_b64_tr_b16 %2, %16 offset:8\n"
-      "ds_read_b64_tr_b16 %3, %16 offset:4136\n"
-      "ds_read_b64_tr_b16 %4, %17\n"
-      "ds_read_b64_tr_b16 %5, %17 offset:4128\n"
-      "ds_read_b64_tr_b16 %6, %17 offset:8\n"
-      "ds_read_b64_tr_b16 %7, %17 offset:4136\n"
-      "ds_read_b64_tr_b16 %8, %18\n"
-      "ds_read_b64_tr_b16 %9, %18 offset:4128\n"
-      "ds_read_b64_tr_b16 %10, %18 offset:8\n"
-      "ds_read_b64_tr_b16 %11, %18 offset:4136\n"
-      "ds_read_b64_tr_b16 %12, %19\n"
-      "ds_read_b64_tr_b16 %13, %19 offset:4128\n"
-      "ds_read_b64_tr_b16 %14, %19 offset:8\n"
-      "ds_read_b64_tr_b16 %15, %19 offset:4136\n"
-      "s_waitcnt lgkmcnt(0)"
-      : "=&v"(x[0]), "=&v"(x[1]), "=&v"(x[2]), "=&v"(x[3]), "=&v"(x[4]), "=&v"(x[5]), "=&v"(x[6]), "=&v"(x[7]),
-        "=&v"(x[8]), "=&v"(x[9]), "=&v"(x[10]), "=&v"(x[11]), "=&v"(x[12]), "=&v"(x[13]), "=&v"(x[14]),
-        "=&v"(x[15])
-      : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]));
-#pragma unroll
-  for (int dt = 0; dt < 8; ++dt) {
-    const uint64_t lo = x[2 * dt], hi = x[2 * dt + 1];
-    vt[dt] = as_bf16x8(u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)});
-  }
-}
+// The transposing LDS read ds_read_b64_tr_b16 forms the transposed operands (V^T in the forward's block mode)
+// of all 8 d-tiles straight from such a tile.  Within each 16-lane group that read hands lane i, element j,
+// element i%4 of the 8 bytes that lane 4j + i/4 addressed.  Addresses a[j] = tile + tr_lane_off(lane, j)
+// serve d-tiles 2j and 2j+1, k-slots 0..3; +8 selects the odd d-tile, +kRmHighRows (4128) the k-slots 4..7
+// (tile rows 16..31).  Result vt[dt], slot k of lane l: row[key slot 16*(k/4) + 4*(l/16) + k%4]
+// [d = 32*((l%16)/4) + 4*dt + l%4], so accumulator register r of d-tile dt in lane l holds
+// d = 32*(l/16) + 4*dt + r.
+static_assert(kRmHighRows == 4128, "the kernels' read offsets are kRmHighRows and kRmHighRows + 8");
 
 // Slot table of one split for the block-mode kernels: row offset (16-byte units) and position of
 // every key slot in [0, nslots), entries e_begin .. e_end-1 of the key list (gathered idx entries,

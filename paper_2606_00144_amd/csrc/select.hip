@@ -1005,9 +1005,8 @@ SelectPlan plan_select(int S, int Hkv, int Hq, int W, int max_L, bool paged, int
   // Keys per split.  A CU holds one workgroup, so the launch runs in rounds of kTargetBlocks workgroups and
   // the count that ends first is taken: rounds x (a split's keys + the fixed cost of a workgroup, ~7 us
   // beside 2 us per 256 keys).  Just filling the CUs once, 18 sequences of 20K with 8 KV heads (144 units)
-  // took two splits each, 288 workgroups in two rounds, the second nearly empty; with five
-  // each (2.8 rounds of a fifth) the two passes take 129 + 141 us there instead of 226 + 210 (the row
-  // tiles of this kernel included).
+  // took two splits each, 288 workgroups in two rounds, the second nearly empty; with five each (2.8 rounds
+  // of a fifth) the two passes take 129 + 141 us there instead of 226 + 210 (the 32x32 row tiles included).
   // Only the largest split counts of 1, 2, ... whole rounds can be best.
   constexpr int64_t kFixedKeys = 768;
   const int64_t whole = max_L > 0 ? (max_L + kStep - 1) / kStep * kStep : kStep;
