@@ -61,7 +61,7 @@ class KvDesc(ctypes.Structure):
 
 _P = ctypes.c_void_p
 _I32, _I64, _F32, _SZ = ctypes.c_int32, ctypes.c_int64, ctypes.c_float, ctypes.c_size_t
-_KV = ctypes.c_void_p        # a KvDesc (byref, pointer) or its bytes
+_KV = ctypes.POINTER(KvDesc)
 _KV_BYTES = struct.Struct("@PPiiiiPqqqPiiiq")
 assert _KV_BYTES.size == ctypes.sizeof(KvDesc)
 _BF16, _I32T, _F32T = torch.bfloat16, torch.int32, torch.float32
@@ -93,6 +93,7 @@ _SIGNATURES = {
 }
 
 _lib = None
+_packed = None               # the same entries taking the descriptor as its bytes (this file's calls alone)
 _lib_lock = threading.Lock()
 
 
@@ -101,19 +102,32 @@ def lib() -> ctypes.CDLL:
     return _lib if _lib is not None else _load()
 
 
+def _bind(kv_type) -> ctypes.CDLL:
+    handle = ctypes.CDLL(library_path)
+    for name, (res, args) in _SIGNATURES.items():
+        fn = getattr(handle, name)
+        fn.restype = res
+        fn.argtypes = [kv_type if a is _KV else a for a in args]
+    return handle
+
+
 def _load() -> ctypes.CDLL:
-    global _lib
+    global _lib, _packed
     with _lib_lock:
         if _lib is None:
             if not os.path.exists(library_path):
                 raise BdError(BD_ERR_DEVICE, f"{library_path} is not built; run `python -m paper_2606_00144_amd.build`")
-            handle = ctypes.CDLL(library_path)
-            for name, (res, args) in _SIGNATURES.items():
-                fn = getattr(handle, name)
-                fn.restype = res
-                fn.argtypes = args
-            _lib = handle
+            # a CDLL of its own holds its own prototypes over the one loaded library
+            _packed = _bind(ctypes.c_char_p)
+            _lib = _bind(_KV)
     return _lib
+
+
+def _packed_lib() -> ctypes.CDLL:
+    """The library's entries with the cache descriptor as the bytes that _kv packs."""
+    if _lib is None:
+        _load()
+    return _packed
 
 
 @functools.lru_cache(maxsize=1024)
@@ -295,8 +309,8 @@ def _select(entry, mode_args, ld, k, q_win, seq_lens, budget, scale, lse_win, re
         _require(lse_win.dtype == torch.float32 and lse_win.is_contiguous() and lse_win.shape == (S, W, Hq), "lse_win must be fp32 [S,W,Hq]")
     stream = _stream()
     wp, wb = _ws("select", _ws_bytes("bd_select_kv_workspace_bytes", S, hkv, Hq, W, L), q_win, stream, workspace)
-    _check(getattr(lib(), entry)(kv, q_win.data_ptr(), Hq, W, budget, *mode_args, _scale(scale),
-                                 _ptr(lse_win), idx.data_ptr(), nsel.data_ptr(), _ptr(scores), wp, wb, stream))
+    _check(getattr(_packed_lib(), entry)(kv, q_win.data_ptr(), Hq, W, budget, *mode_args, _scale(scale),
+                                         _ptr(lse_win), idx.data_ptr(), nsel.data_ptr(), _ptr(scores), wp, wb, stream))
     return (idx, nsel, scores) if return_scores else (idx, nsel)
 
 
@@ -321,8 +335,8 @@ def bd_sparse_decode_attn(k: torch.Tensor, v: torch.Tensor, q: torch.Tensor, idx
     lse = _out(lse, (S, Hq), _F32T, q, "lse") if return_lse else None
     stream = _stream()
     wp, wb = _ws("decode", _ws_bytes("bd_sparse_decode_attn_workspace_bytes", S, hkv, Hq, ld), q, stream, workspace)
-    _check(lib().bd_sparse_decode_attn(kv, q.data_ptr(), Hq, idx.data_ptr(), ld, nsel.data_ptr(), _scale(scale),
-                                       out.data_ptr(), _ptr(lse), wp, wb, stream))
+    _check(_packed_lib().bd_sparse_decode_attn(kv, q.data_ptr(), Hq, idx.data_ptr(), ld, nsel.data_ptr(), _scale(scale),
+                                               out.data_ptr(), _ptr(lse), wp, wb, stream))
     return (out, lse) if return_lse else out
 
 
@@ -354,9 +368,9 @@ def bd_multiview_attn(k: torch.Tensor, v: torch.Tensor, q_blk: torch.Tensor, idx
     stream = _stream()
     nb = _ws_bytes("bd_multiview_attn_workspace_bytes", S, hkv, Hq, C, V, ld, L, int(full))
     wp, wb = _ws("multiview", nb, q_blk, stream, workspace)
-    _check(lib().bd_multiview_attn(kv, q_blk.data_ptr(), Hq, C, V, _ptr(idx_views), ld, _ptr(nsel_views),
-                                   _scale(scale), _ptr(out_v), _ptr(lse_v), _ptr(o32_v), _ptr(out_f), _ptr(lse_f),
-                                   _ptr(o32_f), wp, wb, stream))
+    _check(_packed_lib().bd_multiview_attn(kv, q_blk.data_ptr(), Hq, C, V, _ptr(idx_views), ld, _ptr(nsel_views),
+                                           _scale(scale), _ptr(out_v), _ptr(lse_v), _ptr(o32_v), _ptr(out_f), _ptr(lse_f),
+                                           _ptr(o32_f), wp, wb, stream))
     return (out_v, out_f, o32_v, lse_v, o32_f, lse_f) if train else (out_v, out_f)
 
 
@@ -396,10 +410,10 @@ def bd_multiview_attn_bwd(k: torch.Tensor, v: torch.Tensor, q_blk: torch.Tensor,
     stream = _stream()
     nb = _ws_bytes("bd_multiview_attn_bwd_workspace_bytes", S, hkv, Hq, C, V, ld, L, int(full))
     wp, wb = _ws("multiview_bwd", nb, q_blk, stream, workspace)
-    _check(lib().bd_multiview_attn_bwd(kv, q_blk.data_ptr(), Hq, C, V, _ptr(idx_views), ld,
-                                       _ptr(nsel_views), _scale(scale), _ptr(out32_views), _ptr(lse_views),
-                                       _ptr(dout_views), _ptr(out32_full), _ptr(lse_full), _ptr(dout_full),
-                                       dq.data_ptr(), _ptr(dk), _ptr(dv), wp, wb, stream))
+    _check(_packed_lib().bd_multiview_attn_bwd(kv, q_blk.data_ptr(), Hq, C, V, _ptr(idx_views), ld,
+                                               _ptr(nsel_views), _scale(scale), _ptr(out32_views), _ptr(lse_views),
+                                               _ptr(dout_views), _ptr(out32_full), _ptr(lse_full), _ptr(dout_full),
+                                               dq.data_ptr(), _ptr(dk), _ptr(dv), wp, wb, stream))
     return dq, dk, dv
 
 
@@ -419,7 +433,7 @@ def bd_verify_attn(k: torch.Tensor, v: torch.Tensor, q: torch.Tensor, seq_lens: 
     lse = _out(lse, (S, R, Hq), _F32T, q, "lse") if return_lse else None
     stream = _stream()
     wp, wb = _ws("verify", _ws_bytes("bd_verify_attn_workspace_bytes", S, hkv, Hq, gamma, L), q, stream, workspace)
-    _check(lib().bd_verify_attn(kv, q.data_ptr(), Hq, gamma, _scale(scale), out.data_ptr(), _ptr(lse), wp, wb, stream))
+    _check(_packed_lib().bd_verify_attn(kv, q.data_ptr(), Hq, gamma, _scale(scale), out.data_ptr(), _ptr(lse), wp, wb, stream))
     return (out, lse) if return_lse else out
 
 
@@ -433,8 +447,8 @@ def bd_verify_attn_noalloc(k: torch.Tensor, v: torch.Tensor, q: torch.Tensor, se
     if lse is not None:
         _require(lse.dtype == torch.float32 and lse.shape == q.shape[:3] and lse.is_contiguous(), "lse must be fp32 [S,gamma+1,Hq]")
     kv = _kv(k, v, seq_lens, page_table, max_seq_len)[0]
-    _check(lib().bd_verify_attn_noalloc(kv, q.data_ptr(), q.shape[2], q.shape[1] - 1, _scale(scale),
-                                        out.data_ptr(), _ptr(lse), _stream()))
+    _check(_packed_lib().bd_verify_attn_noalloc(kv, q.data_ptr(), q.shape[2], q.shape[1] - 1, _scale(scale),
+                                                out.data_ptr(), _ptr(lse), _stream()))
 
 
 def bd_accept_len(logits: torch.Tensor, draft: torch.Tensor, *, return_argmax: bool = False,
@@ -473,8 +487,8 @@ def bd_cache_append(k: torch.Tensor, v: torch.Tensor, seq_lens: torch.Tensor, k_
         _require(nsel is not None and nsel.dtype == torch.int32 and nsel.is_contiguous(), "nsel must be int32 [S]")
     kv, S, hkv, _ = _kv(k, v, seq_lens, page_table, max_seq_len)
     _require(k_new.shape[0] == S and k_new.shape[2] == hkv, "k_new must be [S,n,Hkv,128]")
-    _check(lib().bd_cache_append(kv, k_new.data_ptr(), v_new.data_ptr(), k_new.shape[1], _ptr(idx),
-                                 idx.shape[2] if idx is not None else 0, _ptr(nsel), _stream()))
+    _check(_packed_lib().bd_cache_append(kv, k_new.data_ptr(), v_new.data_ptr(), k_new.shape[1], _ptr(idx),
+                                         idx.shape[2] if idx is not None else 0, _ptr(nsel), _stream()))
 
 
 def bd_cache_rollback(seq_lens: torch.Tensor, accept: torch.Tensor, spec: int, *,

@@ -1,4 +1,7 @@
 """The binding's packed cache descriptor, on the CPU: the bytes it passes are those of a KvDesc filled field by field."""
+import ctypes
+import os
+
 import pytest
 import torch
 
@@ -45,3 +48,26 @@ def test_descriptor_refusals():
         kw.update(bad)
         with pytest.raises(bd.BdError):
             bd.kv_desc(**kw)
+
+
+def test_library_descriptor_argument():
+    # lib()'s entries take a KvDesc (itself, byref or a pointer) or NULL and refuse anything else.  Every call that
+    # gets through is refused by the library's own checks (head_dim), so nothing is launched.
+    if not os.path.exists(bd.library_path):
+        from paper_2606_00144_amd import build
+        build.build_library()
+    L = bd.lib()
+    d = bd.kv_desc(torch.zeros(5, 2, 24, 128, dtype=torch.bfloat16), None, torch.zeros(5, dtype=torch.int32))
+    d.head_dim = 64
+    rest = {name: [None if t is ctypes.c_void_p else 0 for t in sig[1][1:]] for name, sig in bd._SIGNATURES.items()
+            if name in ("bd_select_kv", "bd_select_kv_chunks", "bd_cache_append", "bd_sparse_decode_attn",
+                        "bd_multiview_attn", "bd_multiview_attn_bwd", "bd_verify_attn", "bd_verify_attn_noalloc")}
+    assert len(rest) == 8
+    rest["bd_select_kv_chunks"][4] = 1                     # chunk is checked before the descriptor
+    for name, args in rest.items():
+        for good in (d, ctypes.byref(d), ctypes.pointer(d)):
+            assert getattr(L, name)(good, *args) == bd.BD_ERR_UNSUPPORTED, name
+        assert getattr(L, name)(None, *args) == bd.BD_ERR_INVALID_ARG, name
+        for bad in (ctypes.addressof(d), bytes(d), bytearray(d), "kv", ctypes.byref(ctypes.c_int64()), 1.0):
+            with pytest.raises(ctypes.ArgumentError):
+                getattr(L, name)(bad, *args)
