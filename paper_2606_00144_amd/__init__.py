@@ -225,7 +225,7 @@ class Workspace:
         if nbytes == 0:
             return None
         buf = self.buf
-        if buf is None or buf.numel() < nbytes + 256 or buf.device != torch.device(device):
+        if buf is None or buf.numel() < nbytes + 256 or (buf.device != device and buf.device != torch.device(device)):
             buf = self.buf = torch.zeros(nbytes + 256, dtype=torch.uint8, device=device)
         return buf
 
@@ -240,11 +240,9 @@ def _ws(op: str, nbytes: int, like: torch.Tensor, stream: int, workspace: Option
         workspace = _default_ws.get(key)
         if workspace is None:
             workspace = _default_ws.setdefault(key, Workspace())
-    if nbytes == 0:
+    buf = workspace.get(nbytes, like.device)     # always asked: a caller's own get decides
+    if buf is None:
         return None, 0
-    buf = workspace.buf
-    if buf is None or buf.numel() < nbytes + 256 or buf.device != like.device:
-        buf = workspace.get(nbytes, like.device)
     base = buf.data_ptr()
     aligned = (base + 255) & ~255
     return aligned, buf.numel() - (aligned - base)

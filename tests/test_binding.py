@@ -71,3 +71,33 @@ def test_library_descriptor_argument():
         for bad in (ctypes.addressof(d), bytes(d), bytearray(d), "kv", ctypes.byref(ctypes.c_int64()), 1.0):
             with pytest.raises(ctypes.ArgumentError):
                 getattr(L, name)(bad, *args)
+
+
+def test_workspace_get_is_asked_by_every_call():
+    # a caller's own Workspace.get (a subclass's, or an object that has nothing else) decides the scratch of each
+    # call, also where a large enough buffer is there and where none is needed
+    like, asked = torch.zeros(1), []
+
+    class Own(bd.Workspace):
+        def get(self, nbytes, device):
+            asked.append((nbytes, torch.device(device)))
+            self.buf = None                         # a fresh buffer per call
+            return super().get(nbytes, device)
+
+    class Bare:
+        def __init__(self):
+            self.mine = torch.zeros(4096, dtype=torch.uint8)
+
+        def get(self, nbytes, device):
+            asked.append((nbytes, torch.device(device)))
+            return self.mine if nbytes else None
+
+    for ws in (Own(), Bare()):
+        asked.clear()
+        for n in (1000, 500, 0):
+            p, size = bd._ws("op", n, like, 0, ws)
+            assert (p is None and size == 0) if n == 0 else (p % 256 == 0 and size >= n)
+        assert asked == [(n, like.device) for n in (1000, 500, 0)]
+    kept = bd.Workspace()
+    first = bd._ws("op", 1000, like, 0, kept)
+    assert bd._ws("op", 500, like, 0, kept) == first and kept.buf.numel() == 1256
