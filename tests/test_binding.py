@@ -37,6 +37,17 @@ def test_descriptor_bytes(paged, with_v, token_major, L):
     assert bd._kv(k, v, lens, table, L)[0] == want
 
 
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("L", [None, 7, 2 ** 31 - 1, 2 ** 31, 2 ** 33 + 5, -1])
+def test_descriptor_sizes(paged, L):
+    # the sizes that outputs and scratch are allocated by are those of the descriptor's own fields
+    k = torch.zeros(5, 2, 24, 128, dtype=torch.bfloat16)
+    lens = torch.zeros(3 if paged else 5, dtype=torch.int32)
+    table = torch.zeros(3, 4, dtype=torch.int32) if paged else None
+    d = bd.kv_desc(k, None, lens, table, L)
+    assert bd._kv(k, None, lens, table, L)[1:] == (d.num_seqs, d.num_kv_heads, d.max_seq_len)
+
+
 def test_descriptor_refusals():
     k = torch.zeros(5, 2, 24, 128, dtype=torch.bfloat16)
     lens = torch.zeros(5, dtype=torch.int32)
