@@ -192,15 +192,19 @@ __device__ inline void read_tile(TileRegs<NT, PAGED>& T, uint32_t src, uint32_t 
 // at 8 KiB past that, 16 bytes a lane.  Both bring four whole 256-byte rows, a V row's chunks in order, a
 // K row's chunks permuted (k_swizzle) so that the score operands read without bank conflicts.
 // Row offsets are clamped to the layout's extent (validated on the host), so no value can address
-// outside the K/V allocation.  `stream`: the rows are read once per call (the full branch of verify) and
-// load non-temporally.  Gathered lists keep the default: the drafts re-read their entries.
+// outside the K/V allocation.  STREAM_K, stream_v: the rows are read once per call (the full branch of
+// verify) and load non-temporally.  Gathered lists keep the default: the drafts re-read their entries.
 // Whole rows matter: with each lane fetching its own 64 bytes of a key row (an instruction then touches
 // 16 rows in 16-byte parts) K needed the caches to combine four parts of a line and lost under the
 // non-temporal policy.  Measured with whole rows, K and V non-temporal: 64 ragged MHA sequences of 4K-16K
 // in 16-row pages 1617 -> 1526 us (6.5 TB/s); a captured round of 8 sequences at 16K 200 -> 189 us, as
-// verify's K no longer evicts the drafts' rows and the logits from the memory-side cache.
+// verify's K no longer evicts the drafts' rows and the logits from the memory-side cache.  The policy's own
+// share, on K of 32 / 128 / 192 / 256 / 320 MiB (8 sequences, GQA-4): the round 89.3 -> 86.9, 117.2 -> 119.3,
+// 137.5 -> 140.3, 162.4 -> 156.4, 188.9 -> 180.8 us; verify over caches it has not just read -1..-3%; verify again
+// and again on one cache, which finds part of K in that memory, +2..+8% at 128-256 MiB and nothing beyond.
+template <bool STREAM_K>
 __device__ inline void dma_tile(const KvView& kv, const TileRows& A, uint32_t max_roff, uint8_t* dst, int lane,
-                                bool stream) {
+                                bool stream_v) {
   const int lg = lane >> 4, lr = lane & 15;
   const int kc = lr ^ (int)k_swizzle(4 * lg);
 #pragma unroll
@@ -209,7 +213,7 @@ __device__ inline void dma_tile(const KvView& kv, const TileRows& A, uint32_t ma
     for (int i = 0; i < 4; ++i) {
       const uint32_t ro = A.r[h][i] < max_roff ? A.r[h][i] : max_roff;
       const uint16_t* kr = kv.k + ((uint64_t)ro << 3) + 8 * (kc ^ (2 * i));   // k_swizzle(4*lg + i) = k_swizzle(4*lg) ^ 2i
-      if (stream) dma16_nt(kr, dst + (4 * h + i) * 1024);
+      if constexpr (STREAM_K) dma16_nt(kr, dst + (4 * h + i) * 1024);
       else dma16(kr, dst + (4 * h + i) * 1024);
     }
 #pragma unroll
@@ -217,7 +221,7 @@ __device__ inline void dma_tile(const KvView& kv, const TileRows& A, uint32_t ma
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const uint32_t ro = A.r[h][i] < max_roff ? A.r[h][i] : max_roff;
-      if (stream) dma16_nt(kv.v + ((uint64_t)ro << 3) + 8 * lr, dst + (8 + 4 * h + i) * 1024);
+      if (stream_v) dma16_nt(kv.v + ((uint64_t)ro << 3) + 8 * lr, dst + (8 + 4 * h + i) * 1024);
       else dma16(kv.v + ((uint64_t)ro << 3) + 8 * lr, dst + (8 + 4 * h + i) * 1024);
     }
 }
@@ -419,6 +423,12 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p) {
   if constexpr (BY_LENGTH) s = nth_longest(p.kv.seq_lens, p.S, p.kv.max_seq_len, s, L_first);
   const int unit = gather ? pair * p.n_rb + rb : p.units_g + pair * p.n_rb + rb;
 
+  int first_page = -1;                     // paged: the first page of sequence s/64*64 + lane
+  if constexpr (PAGED && !BY_LENGTH) {
+    const int i = (s & ~(kWave - 1)) + lane;
+    if (!gather && p.kv.max_seq_len > 0 && i < p.S) first_page = p.kv.page_table[(int64_t)i * p.kv.max_pages_per_seq];
+  }
+
   // ---- prologue: every load it needs (cache length, entry count, query rows, the split's idx
   // entries) is issued before any of them is used, so they share one memory round trip
   const int L_raw = BY_LENGTH ? L_first : p.kv.seq_lens[s];
@@ -475,6 +485,17 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p) {
     }
   }
 
+  // Pages shared by several sequences (a common prompt) are read once per sequence, so their K keeps the
+  // default policy and is found in the L2.  They count as shared when another of the 64 sequences starts with
+  // the same page.  All sequences on the same pages: 16 x 32K, 16-row pages, 273 -> 198 us (24-row pages 400 ->
+  // 332), 8 x 16K 90.3 -> 83.7; with a branch per tile instead of a loop of its own, 85.0, and every other
+  // verify 1% slower.  Not in the longest-first order, which spreads the heads of a sequence over the XCDs, so
+  // that an L2 meets fewer of the sharing readers (64 x 4K: 75.4 us with either policy, 79.4 with both loops).
+  bool own_pages = true;
+  if constexpr (PAGED && !BY_LENGTH) {
+    const int mine = __builtin_amdgcn_readlane(first_page, s & (kWave - 1));
+    own_pages = __builtin_popcountll(__builtin_amdgcn_ballot_w64(first_page == mine)) == 1;
+  }
   const int L = L_raw < 0 ? 0 : (L_raw > p.kv.max_seq_len ? p.kv.max_seq_len : L_raw);
   const int n_keys = gather ? (n_raw < 0 ? 0 : (n_raw > p.ld_idx ? p.ld_idx : n_raw)) : L;
   int rowpos[NT];
@@ -618,20 +639,20 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p) {
         };
       };
       rows_at(kTile * wave);
-      dma_tile(p.kv, A, p.max_roff, slot_a, lane, !gather);
+      dma_tile<true>(p.kv, A, p.max_roff, slot_a, lane, true);
       rows_at(kTile * (wave + kWaves));
-      dma_tile(p.kv, A, p.max_roff, slot_b, lane, !gather);
+      dma_tile<true>(p.kv, A, p.max_roff, slot_b, lane, true);
       for (int it = wave;; it += 2 * kWaves) {
         asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
         read_tile<NT, PAGED>(T, slot_a_lds, koff, lane);
         rows_at(kTile * (it + 2 * kWaves));
-        dma_tile(p.kv, A, p.max_roff, slot_a, lane, !gather);
+        dma_tile<true>(p.kv, A, p.max_roff, slot_a, lane, true);
         tile_step<NT, PAGED>(st, T, qop, rowpos, p.scale_log2, it >= first_dirty, want_lx, pos_at(kTile * it), pass_v(T));
         if (it + kWaves >= ntiles) break;
         asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
         read_tile<NT, PAGED>(T, slot_b_lds, koff, lane);
         rows_at(kTile * (it + 3 * kWaves));
-        dma_tile(p.kv, A, p.max_roff, slot_b, lane, !gather);
+        dma_tile<true>(p.kv, A, p.max_roff, slot_b, lane, true);
         tile_step<NT, PAGED>(st, T, qop, rowpos, p.scale_log2, it + kWaves >= first_dirty, want_lx,
                              pos_at(kTile * (it + kWaves)), pass_v(T));
         if (it + 2 * kWaves >= ntiles) break;
@@ -682,48 +703,57 @@ __global__ __launch_bounds__(kThreads) void attn_kernel(AttnParams p) {
           return (e < e_end && ((vb >> (i >> 2)) & 1u)) ? e : -1;
         };
       };
-      uint32_t vb_a, vb_b;
-      rows_at(kTile * wave, vb_a);
-      dma_tile(p.kv, A, p.max_roff, slot_a, lane, true);
-      rows_at(kTile * (wave + kWaves), vb_b);
-      dma_tile(p.kv, A, p.max_roff, slot_b, lane, true);
-      for (int it = wave;; it += 2 * kWaves) {
-        asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-        read_tile<NT, PAGED>(T, slot_a_lds, koff, lane);
-        const uint32_t vb_now = vb_a;
-        rows_at(kTile * (it + 2 * kWaves), vb_a);
-        dma_tile(p.kv, A, p.max_roff, slot_a, lane, true);
-        tile_step<NT, PAGED>(st, T, qop, rowpos, p.scale_log2, it >= first_dirty, want_lx, pos_at(kTile * it, vb_now),
-                             pass_v(T));
-        if (it + kWaves >= ntiles) break;
-        asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
-        read_tile<NT, PAGED>(T, slot_b_lds, koff, lane);
-        const uint32_t vb_next = vb_b;
-        rows_at(kTile * (it + 3 * kWaves), vb_b);
-        dma_tile(p.kv, A, p.max_roff, slot_b, lane, true);
-        tile_step<NT, PAGED>(st, T, qop, rowpos, p.scale_log2, it + kWaves >= first_dirty, want_lx,
-                             pos_at(kTile * (it + kWaves), vb_next), pass_v(T));
-        if (it + 2 * kWaves >= ntiles) break;
-      }
+      auto run = [&](auto stream_k) {
+        constexpr bool STREAM_K = decltype(stream_k)::value;
+        uint32_t vb_a, vb_b;
+        rows_at(kTile * wave, vb_a);
+        dma_tile<STREAM_K>(p.kv, A, p.max_roff, slot_a, lane, true);
+        rows_at(kTile * (wave + kWaves), vb_b);
+        dma_tile<STREAM_K>(p.kv, A, p.max_roff, slot_b, lane, true);
+        for (int it = wave;; it += 2 * kWaves) {
+          asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+          read_tile<NT, PAGED>(T, slot_a_lds, koff, lane);
+          const uint32_t vb_now = vb_a;
+          rows_at(kTile * (it + 2 * kWaves), vb_a);
+          dma_tile<STREAM_K>(p.kv, A, p.max_roff, slot_a, lane, true);
+          tile_step<NT, PAGED>(st, T, qop, rowpos, p.scale_log2, it >= first_dirty, want_lx, pos_at(kTile * it, vb_now),
+                               pass_v(T));
+          if (it + kWaves >= ntiles) break;
+          asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
+          read_tile<NT, PAGED>(T, slot_b_lds, koff, lane);
+          const uint32_t vb_next = vb_b;
+          rows_at(kTile * (it + 3 * kWaves), vb_b);
+          dma_tile<STREAM_K>(p.kv, A, p.max_roff, slot_b, lane, true);
+          tile_step<NT, PAGED>(st, T, qop, rowpos, p.scale_log2, it + kWaves >= first_dirty, want_lx,
+                               pos_at(kTile * (it + kWaves), vb_next), pass_v(T));
+          if (it + 2 * kWaves >= ntiles) break;
+        }
+      };
+      if (BY_LENGTH || own_pages) run(BoolTag<true>{});
+      else run(BoolTag<false>{});
     } else {
       const uint32_t roff_lds = lds_addr(sm.u.slots.roff);
       const uint32_t tpos_lds = lds_addr(sm.u.slots.tpos);
       auto pos_of = [&](int i) { return (int)T.tp[i >> 2][i & 3]; };
+      auto dma = [&](uint8_t* slot) {
+        if (PAGED && !gather && own_pages) dma_tile<true>(p.kv, A, p.max_roff, slot, lane, true);
+        else dma_tile<false>(p.kv, A, p.max_roff, slot, lane, PAGED && !gather);
+      };
       read_rows(A, roff_lds, kTile * wave, lane);
-      dma_tile(p.kv, A, p.max_roff, slot_a, lane, !gather);
+      dma(slot_a);
       read_rows(A, roff_lds, kTile * (wave + kWaves), lane);
-      dma_tile(p.kv, A, p.max_roff, slot_b, lane, !gather);
+      dma(slot_b);
       for (int it = wave;; it += 2 * kWaves) {
         asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
         read_tile_and_rows<NT, PAGED>(T, A, slot_a_lds, koff, tpos_lds, kTile * it, roff_lds, kTile * (it + 2 * kWaves),
                                       lane);
-        dma_tile(p.kv, A, p.max_roff, slot_a, lane, !gather);
+        dma(slot_a);
         tile_step<NT, PAGED>(st, T, qop, rowpos, p.scale_log2, it >= first_dirty, want_lx, pos_of, pass_v(T));
         if (it + kWaves >= ntiles) break;
         asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
         read_tile_and_rows<NT, PAGED>(T, A, slot_b_lds, koff, tpos_lds, kTile * (it + kWaves), roff_lds,
                                       kTile * (it + 3 * kWaves), lane);
-        dma_tile(p.kv, A, p.max_roff, slot_b, lane, !gather);
+        dma(slot_b);
         tile_step<NT, PAGED>(st, T, qop, rowpos, p.scale_log2, it + kWaves >= first_dirty, want_lx, pos_of, pass_v(T));
         if (it + 2 * kWaves >= ntiles) break;
       }

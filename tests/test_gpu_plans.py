@@ -108,3 +108,35 @@ def test_verify_longest_first(S, Hkv, paged):
         out = bd.bd_verify_attn(bf16_dev(k), bf16_dev(v), bf16_dev(q), i32_dev(lens))
     torch.cuda.synchronize()
     assert_close(bf16_host64(out), O.verify_attn(k, v, q, lens, gamma)[0], f"longest first S={S}")
+
+
+@pytest.mark.parametrize("P", [16, 24])
+@pytest.mark.parametrize("S,Hkv,shared", [(6, 2, "all"), (6, 2, "prefix"), (70, 1, "pairs"), (1, 2, "all"), (40, 8, "all")])
+def test_verify_shared_pages(S, Hkv, shared, P):
+    # sequences that share pages take another load policy; one that starts outside the pool has keys absent from it
+    gamma, G, Lmax = 2, 2, 300
+    g = np.random.default_rng(61)
+    lens = [int(n) for n in g.integers(gamma + 1, Lmax + 1, S)]
+    lens[-1] = Lmax
+    n = (Lmax + P - 1) // P
+    table = (np.arange(S * n) % (4 * n)).reshape(S, n).astype(np.int32)    # sequences 4 apart share every page
+    if shared == "all":
+        table[:] = g.permutation(n)
+    elif shared == "prefix":
+        table = g.permutation(S * n).reshape(S, n).astype(np.int32)
+        table[1::2, :3] = table[1, :3]
+        table[2, 0] = -1
+    pool = int(table.max()) + 1
+    kp, vp = _rand_bits((pool, Hkv, P, 128), 62), _rand_bits((pool, Hkv, P, 128), 63)
+    q = _rand_bits((S, gamma + 1, Hkv * G, 128), 64)
+    case(f"verify shared pages S={S} Hkv={Hkv} {shared} P={P}")
+    out = bd.bd_verify_attn(bf16_dev(kp), bf16_dev(vp), bf16_dev(q), i32_dev(lens), page_table=i32_dev(table),
+                            max_seq_len=Lmax)
+    torch.cuda.synchronize()
+    got = bf16_host64(out)
+    for s in range(0, S, 1 if S <= 8 else 9):
+        if table[s, 0] < 0:
+            assert np.isfinite(got[s]).all()
+            continue
+        rows = [np.ascontiguousarray(np.moveaxis(x[table[s]], 1, 0)).reshape(1, Hkv, n * P, 128) for x in (kp, vp)]
+        assert_close(got[s:s + 1], O.verify_attn(*rows, q[s:s + 1], [lens[s]], gamma)[0], f"shared pages s={s}")
