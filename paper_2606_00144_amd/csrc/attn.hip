@@ -1866,7 +1866,13 @@ AttnPlan plan_attn(int S, int Hkv, int Hq, int nq, int num_views, int ld_idx, in
   // that the last round holds the shortest, and every sequence over all XCDs.  In index order an XCD took a
   // run of sequences, and the ones with the longest finished last (64 ragged MHA sequences of 4K-16K in 16-row
   // pages: 1526 -> 1478 us).  Up to 64 sequences, one a lane; within one round the order does not matter.
-  pl.by_length = pl.units_g == 0 && pl.nsplit_f == 1 && pl.units_f > kTargetBlocks && S >= 2 && S <= kWave;
+  // From 384 keys on: the workgroups wait for the lengths before their query rows, 0.5-2 us of the launch, and
+  // gain by the longest sequence.  Ragged lengths of at most 256 / 384 / 1,024 keys, 9 sequences x 32 heads:
+  // 12.2 -> 11.2, 13.6 -> 12.3, 24.8 -> 19.0 us; equal ones lose 14.0 -> 15.5, 17.6 -> 18.3, 34.2 -> 35.9, and
+  // at 64 sequences x 5 heads, equal, 128 and 256 keys 12.7 -> 13.1 and 15.5 -> 17.6.
+  constexpr int kLongestFirstKeys = 384;
+  pl.by_length = pl.units_g == 0 && pl.nsplit_f == 1 && pl.units_f > kTargetBlocks && S >= 2 && S <= kWave &&
+                 max_L >= kLongestFirstKeys;
   // group counters per unit for the two-level merge (units of more than kMergeGroup splits)
   auto groups = [](int n) { return n > kMergeGroup ? (n + kMergeGroup - 1) / kMergeGroup : 0; };
   const int gg = pl.units_g ? groups(pl.nsplit_g) : 0, gf = pl.units_f ? groups(pl.nsplit_f) : 0;

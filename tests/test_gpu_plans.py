@@ -140,3 +140,25 @@ def test_verify_shared_pages(S, Hkv, shared, P):
             continue
         rows = [np.ascontiguousarray(np.moveaxis(x[table[s]], 1, 0)).reshape(1, Hkv, n * P, 128) for x in (kp, vp)]
         assert_close(got[s:s + 1], O.verify_attn(*rows, q[s:s + 1], [lens[s]], gamma)[0], f"shared pages s={s}")
+
+
+@pytest.mark.parametrize("Lmax", [383, 384, 400])
+@pytest.mark.parametrize("S,Hkv,paged", [(64, 5, False), (9, 32, False), (9, 32, True), (65, 4, False)])
+def test_verify_longest_first_rule(S, Hkv, paged, Lmax):
+    # the order is taken from 384 keys on; lengths from the shortest possible to beyond the layout (taken as Lmax)
+    gamma = 2
+    g = np.random.default_rng(Lmax)
+    lens = [int(n) for n in g.choice([gamma + 1, 40, 257, Lmax - 1, Lmax], S)]
+    k, v = _rand_bits((S, Hkv, Lmax, 128), 71), _rand_bits((S, Hkv, Lmax, 128), 72)
+    q = _rand_bits((S, gamma + 1, Hkv, 128), 73)
+    given = [n + 9 if n == Lmax else n for n in lens]
+    case(f"verify longest first S={S} Hkv={Hkv} Lmax={Lmax} paged={paged}")
+    if paged:
+        n = (Lmax + 15) // 16
+        table = g.permutation(S * n).reshape(S, n).astype(np.int32)
+        kd, vd = paged_kv(list(k), list(v), table, S * n, 16)
+        out = bd.bd_verify_attn(kd, vd, bf16_dev(q), i32_dev(given), page_table=i32_dev(table), max_seq_len=Lmax)
+    else:
+        out = bd.bd_verify_attn(bf16_dev(k), bf16_dev(v), bf16_dev(q), i32_dev(given))
+    torch.cuda.synchronize()
+    assert_close(bf16_host64(out), O.verify_attn(k, v, q, lens, gamma)[0], f"longest first S={S} Lmax={Lmax}")
