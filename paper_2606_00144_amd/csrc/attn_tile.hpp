@@ -191,17 +191,17 @@ __device__ inline void fill_slot_table(const KvView& kv, int s, int g, int L, co
 template <int WG, int WF, int ROUND = 1>
 struct StreamCut {
   int vt, total, chunk;   // chunk: weight per workgroup
-  __device__ StreamCut(int vt_, int total_, int nW) : vt(vt_), total(total_) {
+  __host__ __device__ StreamCut(int vt_, int total_, int nW) : vt(vt_), total(total_) {
     const int tw = WG * vt + WF * (total - vt);
     int c = (tw + nW - 1) / nW;
     c = (c + ROUND - 1) / ROUND * ROUND;
     chunk = c > WG * 32 ? c : WG * 32;
   }
-  __device__ int weight(int x) const { return x <= vt ? WG * x : WG * vt + WF * (x - vt); }
+  __host__ __device__ int weight(int x) const { return x <= vt ? WG * x : WG * vt + WF * (x - vt); }
   // workgroup whose share holds stream position x
-  __device__ int wg_of(int x) const { return weight(x) / chunk; }
+  __host__ __device__ int wg_of(int x) const { return weight(x) / chunk; }
   // first stream position of workgroup w's share (clamped to the stream's end)
-  __device__ int start_of(int w) const {
+  __host__ __device__ int start_of(int w) const {
     const int t = w * chunk;
     const int x = t <= WG * vt ? (t + WG - 1) / WG : vt + (t - WG * vt + WF - 1) / WF;
     return x < total ? x : total;
