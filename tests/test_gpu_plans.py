@@ -1,4 +1,4 @@
-"""GPU parity where the launch plans change their split: rounds of workgroups, shares and tables at their limits.
+"""GPU parity where the launch plans change their split: rounds of workgroups, and shares that fill the slot tables.
 
 Each case sits at the edge of a planning rule (one workgroup count to the next, a share above the size that
 earlier tables held, a remainder in the last round) and is compared with the fp64 oracle at the tolerances of
@@ -162,3 +162,45 @@ def test_verify_longest_first_rule(S, Hkv, paged, Lmax):
         out = bd.bd_verify_attn(bf16_dev(k), bf16_dev(v), bf16_dev(q), i32_dev(given))
     torch.cuda.synchronize()
     assert_close(bf16_host64(out), O.verify_attn(k, v, q, lens, gamma)[0], f"longest first S={S} Lmax={Lmax}")
+
+
+@pytest.mark.parametrize("V,ld,L", [
+    (1, 900, 3196), (1, 900, 3197),      # the backward's table filled to the entry by one workgroup; one more: two
+    (0, 0, 4063), (0, 0, 4064),          # the forward's, one branch
+    (4, 1, 3930), (4, 1, 3931),          # the forward's with five branches, four of them a padded tile for one entry
+])
+def test_block_tables_filled(V, ld, L):
+    # 256 units (8 sequences x 8 KV heads x 4 row groups): one workgroup takes a unit's whole stream if it can hold it
+    S, Hkv, G, C = 8, 8, 4, 256
+    lens = [L] * S
+    k, v = _rand_bits((S, Hkv, L, 128), 310), _rand_bits((S, Hkv, L, 128), 311)
+    qb = _rand_bits((S, C, Hkv * G, 128), 312)
+    g = np.random.default_rng(313)
+    idx_v = nsel_v = None
+    if V:
+        idx_v = np.stack([np.sort(g.choice(L, ld, replace=False)) for _ in range(V * S * Hkv)])
+        idx_v = idx_v.reshape(V, S, Hkv, ld).astype(np.int32)
+        nsel_v = np.full((V, S), ld, np.int32)
+    _run(k, v, qb, idx_v, nsel_v, lens, f"filled V={V} ld={ld} L={L}", seqs=[7], seed=8)
+
+
+@pytest.mark.parametrize("Hkv,C,V,ld,L", [(1, 16, 1, 32, 256), (2, 32, 1, 128, 1024), (1, 1, 0, 0, 32), (1, 1, 0, 0, 33),
+                                          (4, 40, 1, 1, 64), (1, 16, 2, 31, 7)])
+def test_backward_short_streams(Hkv, C, V, ld, L):
+    # as many workgroups as the stream has tiles, one and two tiles, lists shorter than the stream that was planned.
+    # Some row sees two keys or more: over a single key dQ is exactly zero, and the tolerance, a fraction of the
+    # largest gradient, has nothing to hold the rounding of dP - D (128 fp32 products, about 1e-7) against.
+    S, G = 2, 2
+    lens = [L, max(1, L // 3)]
+    k, v = _rand_bits((S, Hkv, L, 128), 320), _rand_bits((S, Hkv, L, 128), 321)
+    qb = _rand_bits((S, C, Hkv * G, 128), 322)
+    g = np.random.default_rng(323)
+    idx_v = nsel_v = None
+    if V:
+        nsel_v = np.array([[min(ld, n) for n in lens]] * V, np.int32)
+        idx_v = np.full((V, S, Hkv, ld), -1, np.int32)
+        for i in range(V):
+            for s in range(S):
+                for h in range(Hkv):
+                    idx_v[i, s, h, :nsel_v[i, s]] = np.sort(g.choice(lens[s], nsel_v[i, s], replace=False))
+    _run(k, v, qb, idx_v, nsel_v, lens, f"short stream Hkv={Hkv} C={C} V={V} ld={ld} L={L}", seed=9)
