@@ -21,8 +21,11 @@ __device__ inline void dma16_nt(const uint16_t* g, uint8_t* l) {
 
 // The same issued by hand, at an LDS address: the compiler's wait analysis does not see it, so ordinary LDS
 // reads beside it wait for LDS alone (it would otherwise wait for every such load in flight before any LDS
-// read).  The kernel waits for its tiles explicitly.  M0 is a reserved register: the compiler keeps nothing
-// in it across statements.
+// read).  The kernel waits for its tiles explicitly.  M0 (the load's LDS base) is named as clobbered: the
+// compiler reuses it between the loads that it places itself, and one of those after a load of these would go
+// to the other's address.  It warns that M0 is reserved; it keeps no value of its own there that must survive.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ inline void dma16_hidden(const uint16_t* g, uint32_t lds) {
   asm volatile(
       "s_mov_b32 m0, %0\n"
@@ -30,8 +33,19 @@ __device__ inline void dma16_hidden(const uint16_t* g, uint32_t lds) {
       "global_load_lds_dwordx4 %1, off"
       :
       : "s"(lds), "v"(g)
-      : "memory");
+      : "memory", "m0");
 }
+// The same with a uniform base and a byte offset per lane (32 bits).
+__device__ inline void dma16_hidden(const uint16_t* base, uint32_t voff, uint32_t lds) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n"
+      "s_nop 0\n"
+      "global_load_lds_dwordx4 %1, %2"
+      :
+      : "s"(lds), "v"(voff), "s"(base)
+      : "memory", "m0");
+}
+#pragma clang diagnostic pop
 
 // ---- 32-row tiles for v_mfma_f32_32x32x16_bf16 ---------------------------------
 //

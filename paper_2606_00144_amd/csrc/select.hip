@@ -27,6 +27,7 @@
 
 #include "bd_common.hpp"
 #include "bd_kernels.hpp"
+#include "attn_tile.hpp"
 
 namespace bd {
 namespace {
@@ -75,8 +76,6 @@ __device__ inline int fetch_select_args(const SelectParams& p) {
   return z2;
 }
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
 template <int RT, bool PAGED>
 struct ScoreSmem {
   alignas(64) uint8_t ring[kWaves][kRing][kTileBytes];   // per-wave K tile slots filled by DMA
@@ -85,20 +84,6 @@ struct ScoreSmem {
   float l[kWaves][32 * RT];
   float lse2[32 * RT];
 };
-
-// One 16-byte direct-to-LDS load: lane l's bytes land at LDS address `dst` + 16*l.  Issued by hand so that
-// the compiler's wait analysis does not see it: it would otherwise wait for every such load in flight
-// before any LDS read.  The waits are explicit (vmcnt before a tile is read).  M0 is a reserved register:
-// the compiler keeps nothing in it, and nothing else in these kernels uses it.
-__device__ inline void dma16(const uint16_t* g, uint32_t dst) {
-  asm volatile(
-      "s_mov_b32 m0, %0\n"
-      "s_nop 0\n"
-      "global_load_lds_dwordx4 %1, off"
-      :
-      : "s"(dst), "v"(g)
-      : "memory");
-}
 
 // Direct-to-LDS loads of one K tile: load (h, i) brings the four whole rows 16h + 4*(lane/16) + i to
 // dst + (4h + i) KiB, 16 bytes a lane; r[h][i] are the lane's rows (16-byte units, clamped to the
@@ -112,7 +97,7 @@ __device__ inline void dma_ktile(const uint16_t* k, const u32x4 (&r)[2], uint32_
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const uint32_t ro = r[h][i] < max_roff ? r[h][i] : max_roff;
-      dma16(k + ((uint64_t)ro << 3) + 8 * (kc ^ (2 * i)), dst + (4 * h + i) * 1024);   // swizzle of row 4*lg + i
+      dma16_hidden(k + ((uint64_t)ro << 3) + 8 * (kc ^ (2 * i)), dst + (4 * h + i) * 1024);   // swizzle of row 4*lg + i
     }
 }
 // Byte offset in a tile of chunk 8*(lane/32) of row lane%32; chunk + j is at this ^ 16*j.
@@ -125,15 +110,6 @@ __device__ inline uint32_t k_lane_off(int lane) {
 // The same for a tile whose two 16-key sub-tiles are runs of rows `stride` bytes apart, from uniform byte
 // offsets base[h] into K: the address of a load is a scalar base plus a lane-constant offset, so a tile
 // costs few vector instructions.  The caller knows that all 32 rows lie in the layout.
-__device__ inline void dma16_run(const uint16_t* base, uint32_t voff, uint32_t dst) {
-  asm volatile(
-      "s_mov_b32 m0, %0\n"
-      "s_nop 0\n"
-      "global_load_lds_dwordx4 %1, %2"
-      :
-      : "s"(dst), "v"(voff), "s"(base)
-      : "memory");
-}
 __device__ inline void dma_krun(const uint16_t* k, const uint64_t (&base)[2], uint32_t stride, uint32_t dst) {
   // the lane offsets are formed again for each tile, from the lane index up: kept across the loop they
   // cost spills, and a reload waits for every load in flight
@@ -149,7 +125,7 @@ __device__ inline void dma_krun(const uint16_t* k, const uint64_t (&base)[2], ui
     const uint32_t voff = voff_row + (voff_chunk ^ (32u * (uint32_t)i));
 #pragma unroll
     for (int h = 0; h < 2; ++h)
-      dma16_run(reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(k) + base[h] + (uint64_t)((uint32_t)i * stride)),
+      dma16_hidden(reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(k) + base[h] + (uint64_t)((uint32_t)i * stride)),
                 voff, dst + (4 * h + i) * 1024);
   }
 }
@@ -320,7 +296,7 @@ __global__ __launch_bounds__(kThreads) void score_kernel(SelectParams p) {
       const int r = 4 * RT * wave + 4 * q + lg;
       const int n = rb * kRows + r < p.R ? rb * kRows + r : p.R - 1;     // rows past R are dropped when read
       const int i = n / p.G, h = g * p.G + n - i * p.G;
-      dma16(p.q_win + (((int64_t)s * p.W + i) * p.Hq + h) * kD + 8 * ((lane & 15) ^ k_swizzle(r & 15)), dst + q * 1024);
+      dma16_hidden(p.q_win + (((int64_t)s * p.W + i) * p.Hq + h) * kD + 8 * ((lane & 15) ^ k_swizzle(r & 15)), dst + q * 1024);
     }
   }
   int rowpos[RT];
@@ -550,13 +526,6 @@ __global__ __launch_bounds__(kThreads) void score_kernel(SelectParams p) {
       if constexpr (PASS == 1) pass1_sum(acc, t);
       else pass2_sum(acc, t);
     };
-    auto interleave = [] {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);       // one product
-        __builtin_amdgcn_sched_group_barrier(0x402, 6, 0);       // six vector instructions
-      }
-    };
     auto run_clean = [&](int end) {
       if (j >= end) return;
       f32x16 acc[2];
@@ -570,7 +539,7 @@ __global__ __launch_bounds__(kThreads) void score_kernel(SelectParams p) {
         for (int t = 1; t < RT; ++t) {
           products(acc[(par + t) & 1], t);
           sum(acc[(par + t - 1) & 1], t - 1);
-          interleave();
+          interleave_mfma_valu<8, 6>();
         }
         const int tb0 = tb;
         ++j;
@@ -582,7 +551,7 @@ __global__ __launch_bounds__(kThreads) void score_kernel(SelectParams p) {
         tb = read_tile();
         products(acc[(par + RT) & 1], 0);
         sum(acc[(par + RT - 1) & 1], RT - 1);
-        interleave();
+        interleave_mfma_valu<8, 6>();
         if constexpr (PASS == 2) {
           // the reduction after the sums: beside them its temporaries exceeded the registers
           __builtin_amdgcn_sched_barrier(0);
