@@ -106,10 +106,9 @@ struct TileRows {
 // sub-tile was brought by load i = m%4 to byte 1024*i + 256*(m/4), its chunk c at position
 // c ^ k_swizzle(m).  All rows start on the same LDS bank and the swizzle gives the 16 rows 16
 // different positions, so the score reads meet no bank twice.
-__device__ inline uint32_t k_swizzle(int m) { return (uint32_t)(((m & 7) << 1) | (m >> 3)); }
 __device__ inline uint32_t k_lane_off(int lane) {
   const int lg = lane >> 4, lr = lane & 15;
-  return 1024u * (uint32_t)(lr & 3) + 256u * (uint32_t)(lr >> 2) + 16u * ((uint32_t)(4 * lg) ^ k_swizzle(lr));
+  return 1024u * (uint32_t)(lr & 3) + 256u * (uint32_t)(lr >> 2) + 16u * (uint32_t)((4 * lg) ^ k_swizzle(lr));
 }
 
 // Read a tile's row offsets from the LDS slot table: loads and their wait in one asm statement.
@@ -206,7 +205,7 @@ template <bool STREAM_K>
 __device__ inline void dma_tile(const KvView& kv, const TileRows& A, uint32_t max_roff, uint8_t* dst, int lane,
                                 bool stream_v) {
   const int lg = lane >> 4, lr = lane & 15;
-  const int kc = lr ^ (int)k_swizzle(4 * lg);
+  const int kc = lr ^ k_swizzle(4 * lg);
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -1060,7 +1059,7 @@ struct BlockSmem {
 // q < 8 (sub-tile q/4, k-step q%4) land in the score operand order.  V loads q >= 8 fill the
 // tile's second half as a row-major tile for the transposing reads (rm_row, rm_chunk).
 __device__ inline void dma_load(const KvView& kv, uint32_t r, uint32_t max_roff, int q, uint8_t* dst, int lane) {
-  const int lg = lane >> 4, lr = lane & 15;
+  const int lg = lane >> 4;
   const uint32_t ro = r < max_roff ? r : max_roff;
   if (q < 8) dma16(kv.k + ((uint64_t)ro << 3) + 32 * lg + 8 * (q & 3), dst + q * 1024);
   else dma16(kv.v + ((uint64_t)ro << 3) + 8 * rm_chunk(lane), dst + 8192 + rm_block_off(q - 8));

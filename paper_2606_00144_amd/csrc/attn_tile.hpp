@@ -47,6 +47,10 @@ __device__ inline void dma16_hidden(const uint16_t* base, uint32_t voff, uint32_
 }
 #pragma clang diagnostic pop
 
+// Where tiles are read by rows alone (scores): chunk c (16 bytes) of row m of a 16-row sub-tile sits at position
+// c ^ k_swizzle(m), which differs for all 16 rows.
+__device__ inline int k_swizzle(int m) { return ((m & 7) << 1) | (m >> 3); }
+
 // ---- 32-row tiles for v_mfma_f32_32x32x16_bf16 ---------------------------------
 //
 // A tile of 32 rows of 128 bf16 (8 KiB) that serves both kinds of operand reads.  Load (h, i), 0 <= h < 2,

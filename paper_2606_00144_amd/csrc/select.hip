@@ -89,7 +89,6 @@ struct ScoreSmem {
 // dst + (4h + i) KiB, 16 bytes a lane; r[h][i] are the lane's rows (16-byte units, clamped to the
 // layout).  Chunk c (16 bytes) of row m lands at position c ^ k_swizzle(m % 16) of its 256 bytes: all
 // rows start on the same LDS bank, and the swizzle puts the rows of a score read on different ones.
-__device__ inline int k_swizzle(int m) { return ((m & 7) << 1) | (m >> 3); }
 __device__ inline void dma_ktile(const uint16_t* k, const u32x4 (&r)[2], uint32_t max_roff, uint32_t dst, int lane) {
   const int kc = (lane & 15) ^ k_swizzle(4 * (lane >> 4));
 #pragma unroll
