@@ -1792,8 +1792,7 @@ AttnPlan plan_attn(int S, int Hkv, int Hq, int nq, int num_views, int ld_idx, in
   pl.counter_bytes = BD_WS_COUNTER_BYTES;   // fixed: scratch of any call never lands on a counter
   if (pl.block) {
     // workgroups per (sequence, KV head, row group) unit, each taking an equal share of the unit's
-    // key stream: enough to fill the CUs once, and enough that no share (rounded up to whole tiles)
-    // overflows the slot table
+    // key stream: the rounds of the CUs filled, and enough that no share overflows the slot table
     pl.units = sat_count((int64_t)S * Hkv * pl.n_rg);
     pl.nbr = sat_count((int64_t)num_views + (with_full ? 1 : 0));
     if (pl.nbr > kBMaxPieces) {      // more branches than a range holds pieces: not launchable
@@ -1803,7 +1802,9 @@ AttnPlan plan_attn(int S, int Hkv, int Hq, int nq, int num_views, int ld_idx, in
     }
     // a share holds at most weight / (nW * kWFull) + 1 entries, and each of its pieces (one per branch
     // at most) pads its last tile, as do the prefetches past the end: together within the slot table.
-    // nw_hi is the count of a table that knew neither the weights nor the branch count.
+    // nw_hi: one workgroup per CU, or shares of 2,016 entries if that is more workgroups; it bounds the
+    // records (a share leaves one per row block and branch) and the scratch by what they were before the
+    // plan weighed rounds
     const int64_t stream_max = (int64_t)num_views * ld_idx + (with_full ? max_L : 0);
     const int64_t weight = (int64_t)kWGather * num_views * ld_idx + (with_full ? (int64_t)kWFull * max_L : 0);
     const int64_t per_share = (int64_t)kWFull * (kBSlotCap - (pl.nbr + kBRing) * kTile - 1);

@@ -16,11 +16,11 @@
 // dQ kernel.  Like the forward's block mode: a workgroup of 8 waves owns a
 // share of one (sequence, KV head, row group) unit's key stream (the views'
 // entry lists followed by the full branch's cache rows, cut into equal ranges
-// at run time, when the list lengths are known); wave w owns the 32-row block
+// of whole tiles at run time, when the list lengths are known); wave w owns the 32-row block
 // 8*rg + w and every wave consumes every 32-key tile from a shared LDS ring
-// filled by direct-to-LDS loads.  A tile carries K and V in the score operand
-// layout and K a second time in the transposed layout of the dQ product, so
-// every LDS read is a linear 1 KiB per instruction.  Per tile a wave runs
+// filled by direct-to-LDS loads.  A tile holds 32 whole rows of K and of V, their
+// 16-byte chunks swizzled so that one copy serves the row reads (S, dP) and the
+// transposing reads (dQ) without bank conflicts.  Per tile a wave runs
 // three MFMA products (keys on the M side throughout):
 //   S^T  [key][row] = K . Q^T          A = K tile,  B = Q^T   (registers)
 //   dP^T [key][row] = V . dO^T         A = V tile,  B = dO^T  (registers)

@@ -202,8 +202,8 @@ __device__ inline void fill_slot_table(const KvView& kv, int s, int g, int L, co
 // view entry weighing WG and a cache row of the full branch WF (gathered tiles cost more per tile).
 // Views come first, so stream position x (vt = the views' total) weighs WG*x up to vt and WF per
 // row after.  A share weighs at least WG*32, so every workgroup below the stream's end gets entries
-// and the workgroups that meet a branch are consecutive.  All kernels over a unit's stream cut it
-// with the same weights.
+// and the workgroups that meet a branch are consecutive.  Each kernel has weights of its own (the
+// forward 5 and 4, dQ 1 and 1 in whole tiles); none relies on the shares of another.
 // ROUND: the share's weight is rounded up to a multiple of ROUND (with WG = WF = 1 and ROUND = 32,
 // equal shares that start on whole tiles of the stream).
 template <int WG, int WF, int ROUND = 1>
@@ -226,7 +226,8 @@ struct StreamCut {
   }
 };
 // Workgroups per unit for `units` streams of at most `weight` each (weighted as StreamCut weighs them),
-// between nw_lo (no share overflows its slot table) and nw_hi (the scratch planned for).  A CU holds
+// between nw_lo (no share overflows its slot table) and nw_hi (each share leaves records in scratch, which the
+// merge reads).  A CU holds
 // one workgroup of these kernels, so a launch of more than kCus workgroups runs in rounds, and one
 // that just exceeds a multiple leaves its last round nearly empty: 24 units at ceil(256 / 24) = 11
 // each are 264 workgroups, two rounds of a 1/11 share, where 10 each take one round of a 1/10 share

@@ -29,7 +29,7 @@ struct AttnParams {
   int32_t S, Hkv, Hq, G;
   int32_t nq;               // query rows per head (1, gamma+1 or C)
   int32_t R;                // rows per (s, g): nq * G
-  int32_t n_rb;             // row blocks of at most 128 rows
+  int32_t n_rb;             // row blocks of 16 rows (at most 16 rows in all) or 32
   int32_t n_rg;             // block mode: row groups of 8 row blocks (otherwise n_rb)
   int32_t nsplit_g, kps_g;  // gathered units: splits and entries per split
   int32_t nsplit_f, kps_f;  // full units: splits and keys per split

@@ -140,11 +140,10 @@ __device__ inline void read_krows(u32x4 (&r)[2], uint32_t roff_lds, int slot0, i
       : "v"(a));
 }
 
-// Sums of 16 values over the 32 lanes of each half: value i of the result's key order ends in lanes with
-// l%16 == i (both rows of the half hold different values, see below).  Each step halves the values a lane
-// carries and doubles the lanes summed.  Step 1 pairs value i with value i + 8 over lanes 16 apart (one
-// permlane16_swap serves both), the others exchange within a row of 16.
-// Returns the sum that this lane ends up with; its value index is half_sum_index(lane).
+// Sums of 16 values over the 32 lanes of each half: value i ends in lanes 2i and 2i + 1 of the half
+// (half_sum_index).  Each step halves the values a lane carries and doubles the lanes summed: step 1 pairs value
+// i with value i + 8 over lanes 16 apart (one permlane16_swap serves both), the others exchange within a row of
+// 16, the last one over the two lanes that keep the sum.
 __device__ inline float half_sums(const float (&v)[16], int lane) {
   float a[8];
 #pragma unroll
@@ -170,7 +169,7 @@ __device__ inline float half_sums(const float (&v)[16], int lane) {
   return e;
 }
 __device__ inline int half_sum_index(int lane) {
-  return ((lane & 16) >> 1) | ((lane & 8) >> 1) | ((lane & 4) >> 1) | ((lane & 2) >> 1);
+  return (lane & 31) >> 1;
 }
 
 // One pass over the causal key range of (sequence, KV head, row block of 32*RT rows, split).  Each wave
