@@ -186,20 +186,19 @@ def _kv(k, v, seq_lens, page_table=None, max_seq_len=None):
     if page_table is None:
         if n0 != S:
             raise BdError(BD_ERR_INVALID_ARG, "contiguous k must be [S, Hkv, L, 128]")
-        L = _int32(n2 if max_seq_len is None else int(max_seq_len))
+        L = n2 if max_seq_len is None else int(max_seq_len)
+        if L > 0x7FFFFFFF or L < -0x80000000:
+            L = _I32(L).value            # the descriptor's field keeps the low bits; scratch and outputs follow it
         return _pack_kv(k.data_ptr(), vp, S, hkv, HEAD_DIM, L, seq_lens.data_ptr(), st[0], st[1], st[2],
                         0, 0, 0, 0, 0), S, hkv, L
     ps = page_table.shape
     if not (page_table.dtype == _I32T and len(ps) == 2 and ps[0] == S):
         raise BdError(BD_ERR_INVALID_ARG, "page_table must be int32 [S, max_pages]")
-    L = _int32(ps[1] * n2 if max_seq_len is None else int(max_seq_len))
+    L = ps[1] * n2 if max_seq_len is None else int(max_seq_len)
+    if L > 0x7FFFFFFF or L < -0x80000000:
+        L = _I32(L).value
     return _pack_kv(k.data_ptr(), vp, S, hkv, HEAD_DIM, L, seq_lens.data_ptr(), 0, st[1], st[2],
                     page_table.data_ptr(), n2, ps[1], n0, st[0]), S, hkv, L
-
-
-def _int32(n: int) -> int:
-    """What a descriptor's 32-bit field holds of n (its low bits); scratch and output sizes follow the field."""
-    return n if -0x80000000 <= n <= 0x7FFFFFFF else _I32(n).value
 
 
 def _pack_kv(*fields) -> bytes:
@@ -245,7 +244,11 @@ def _ws(op: str, nbytes: int, like: torch.Tensor, stream: int, workspace: Option
         workspace = _default_ws.get(key)
         if workspace is None:
             workspace = _default_ws.setdefault(key, Workspace())
-    buf = workspace.get(nbytes, like.device)     # always asked: a caller's own get decides
+        buf = workspace.buf if nbytes else None      # on `like`'s device: the key holds its index
+        if nbytes and (buf is None or buf.numel() < nbytes + 256):
+            buf = workspace.get(nbytes, like.device)
+    else:
+        buf = workspace.get(nbytes, like.device)     # always asked: a caller's own get decides
     if buf is None:
         return None, 0
     base = buf.data_ptr()

@@ -112,3 +112,20 @@ def test_workspace_get_is_asked_by_every_call():
     kept = bd.Workspace()
     first = bd._ws("op", 1000, like, 0, kept)
     assert bd._ws("op", 500, like, 0, kept) == first and kept.buf.numel() == 1256
+
+
+def test_default_scratch_is_kept_and_grown():
+    # without a caller's workspace: one buffer per (operation, device, stream), kept while it is large enough
+    like = torch.zeros(1)
+    key = ("test_default_scratch", like.get_device(), 7)
+    try:
+        assert bd._ws(key[0], 0, like, 7, None) == (None, 0)
+        p, size = bd._ws(key[0], 1000, like, 7, None)
+        assert p % 256 == 0 and size >= 1000
+        assert bd._ws(key[0], 500, like, 7, None) == (p, size)
+        assert bd._ws(key[0], 0, like, 7, None) == (None, 0)
+        p, size = bd._ws(key[0], 5000, like, 7, None)
+        assert p % 256 == 0 and size >= 5000 and not bd._default_ws[key].buf.any()
+        assert ("test_default_scratch", like.get_device(), 8) not in bd._default_ws
+    finally:
+        bd._default_ws.pop(key, None)
