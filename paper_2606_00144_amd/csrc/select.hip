@@ -580,7 +580,10 @@ __global__ __launch_bounds__(kThreads) void score_kernel(SelectParams p) {
     // merge the 2 lane halves, then the waves, and publish per-row (max, sum) of this split
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
-      if (!(rl[t] > 0.f)) rm[t] = -INFINITY;   // no visible key: the empty (max, sum)
+      // no visible key: the empty (max, sum).  A logit of +inf leaves NaN in one half's sum and 0 in the other's
+      // (they share the reference): under a maximum of +inf the NaN comes through every merge, and the row gives
+      // no key a weight
+      if (!(rl[t] > 0.f)) rm[t] = rl[t] == 0.f ? -INFINITY : INFINITY;
       const float m2 = shfl_xor_f(rm[t], 32), l2 = shfl_xor_f(rl[t], 32);
       merge_ml(rm[t], rl[t], m2, l2);
       if (hf == 0) {

@@ -183,3 +183,36 @@ def test_select_ragged_paged_mha():
     near = _check(ks, np.stack(qw), lens, cfg.num_q_heads, cfg.window, 1024, "ragged paged paged",
                   page_table=i32_dev(table), kdev=kd)
     assert near <= 4
+
+
+@pytest.mark.parametrize("L,at", [(40, 3), (40, 30), (300, 17), (1033, 700), (4097, 4000)])
+def test_row_with_an_infinite_logit(L, at):
+    # One window row's product with one key overflows.  The row's weight belongs to that key, whose score is not a
+    # number; the row gives every other key nothing, and the other rows score as if it were not there.
+    W, G, Hkv, B = 4, 2, 2, 16
+    g = np.random.default_rng(77)
+    q = g.standard_normal((1, W, Hkv * G, 128)).astype(np.float32)
+    k = g.standard_normal((1, Hkv, L, 128)).astype(np.float32)
+    q[..., 5] = 0.0
+    q[0, 1, ::G, 5] = 100.0                      # window row 1, first query head of each KV head
+    k[..., 5] = 0.0
+    k[0, :, at, 5] = 3.0e38
+    qb, kb = synth.f32_to_bf16_bits(q), synth.f32_to_bf16_bits(k)
+    case(f"select infinite logit L={L} at={at}")
+    _, _, sc = bd.bd_select_kv(bf16_dev(kb), bf16_dev(qb), i32_dev([L]), B, return_scores=True)
+    torch.cuda.synchronize()
+    got = sc.cpu().numpy().astype(np.float64)[0]
+    qf, kf = O.bf16_to_f64(qb)[0], O.bf16_to_f64(kb)[0]
+    for h in range(Hkv):
+        want = np.zeros(L)
+        for i in range(W):
+            for j in range(G):
+                if (i, j) == (1, 0):
+                    continue
+                n = L - W + i + 1                # keys that row i sees
+                z = kf[h, :n] @ qf[i, h * G + j] / np.sqrt(128.0)
+                p = np.exp(z - z.max())
+                want[:n] += p / p.sum()
+        others = np.arange(L) != at
+        np.testing.assert_allclose(got[h, others], want[others], rtol=1e-3, atol=1e-6)
+        assert not np.isfinite(got[h, at])
