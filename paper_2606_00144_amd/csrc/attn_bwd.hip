@@ -133,8 +133,8 @@ __device__ inline void interleave_lds_mfma_valu() {
 // one with vector work while the other runs its dQ product.  Measured, with 32x32 products and one K copy in
 // a tile where 16x16 products and two K copies (one for each read) were: 8K, C = 64, four views, 4 sequences
 // 141 -> 114 us; 16K, C = 256 238 -> 196 us (without the raised priority 119 and 208, without the interleaved
-// LDS reads 132 and 221).  What bounds it: at 2.1 us a tile the matrix units are busy 45% of the time and the
-// vector units 30%; the two waves of a SIMD still meet in the same phase.
+// LDS reads 132 and 221).  What bounds it: over the kernel the matrix units are busy 35% of the time and the
+// vector units 34% (16K, C = 256: 46% and 43%); the two waves of a SIMD still meet in the same phase.
 // P and dS never leave registers: a product's result order is the next one's operand order.  dS enters its
 // product as a bf16 pair hi + lo (lo the rounded remainder): where a row's weight concentrates, dS terms of
 // both signs nearly cancel in dQ and a single bf16 rounding of dS would dominate the result's error.

@@ -178,9 +178,10 @@ __device__ inline int half_sum_index(int lane) {
 //   PASS 2: every key's column sum of the rows' normalised weights (complete within the row
 //           block: one plain store per key).
 // Per 32 x 32 scores a wave needs 8 products (32 cycles each) and 48 vector instructions (16 of them
-// exponentials at 8 cycles): the two units have equal work, so the tile loop is pipelined by row tile,
-// products of one beside the exponentials of the one before.  What bounds it: the two units at half of
-// their rates each in the loop (2.0 us per tile and wave pair), and for 128 rows at 16K x 8 the K stream.
+// exponentials at 8 cycles): the two units have like work, so the tile loop is pipelined by row tile,
+// products of one beside the exponentials of the one before.  What bounds it: the chain of the two at two
+// waves per SIMD (over the kernel matrix units 27-30% and vector units 45-48% busy), and for 128 rows at
+// 16K x 8 the K stream, which pass 1 reads from HBM (54-59 us where the caches hold none of it).
 // Measured, 16K keys, passes 1 and 2: 8 sequences, 128 rows 58 + 51 -> 46 + 44.5 us; one sequence, 1,024
 // rows (8 blocks, K from the caches) 57.5 + 50.5 -> 43.5 + 43 us; at 4K, 128 workgroups 14.4 + 12.4 ->
 // 10.6 + 8.3 us.  Before: 16x16x32 products with all of a tile's products ahead of its exponentials, row
