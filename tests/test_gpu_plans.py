@@ -91,8 +91,8 @@ def test_select_split_rounds(S, Hkv):
 @pytest.mark.parametrize("paged", [False, True])
 @pytest.mark.parametrize("S,Hkv", [(64, 5), (9, 32), (65, 4), (2, 160)])
 def test_verify_longest_first(S, Hkv, paged):
-    # more whole units than CUs: up to 64 sequences are taken from the longest to the shortest (65 are not);
-    # equal lengths, the shortest possible and the longest among them
+    # more whole units than CUs, caches too short for the longest-first order (test_verify_longest_first_rule has
+    # both sides of that line); equal lengths, the shortest possible and the longest among them
     gamma, Lmax, Hq = 2, 150, Hkv
     g = np.random.default_rng(47)
     lens = [int(n) for n in g.choice([gamma + 1, 40, 97, 98, 150], S)]
